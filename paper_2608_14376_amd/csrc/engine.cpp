@@ -197,6 +197,56 @@ Proj choose_proj(int N, int K, int M, int split_override, int max_split, int bm_
     return p;
 }
 
+// The same for more than 128 prefill rows: the wide tile (320 x 256, 256 x 256,
+// 256 x 128 or 128 x 128) and split-K of least estimated time.  A launch runs
+// in rounds of 256 workgroups (one per CU; two of 128 x 128 share a CU).  A
+// full round over K / S = 4096 takes `full` us, a round of few workgroups `lo`
+// (the card is power-limited: fewer busy CUs run at a higher clock; in between
+// the cost grows with the square of the filled part), `fixed` of them whatever
+// K (ring fill, epilogue); every split beyond the first adds a set of fp32
+// partials written and folded again (8 bytes per output at about 5 TB/s).
+// Over 4 projections of the 8B shape at 15 lengths from 300 to 8192 rows
+// (128 x 128 at 300 x 4096 x 4096: 25 us; 320 x 256 at 4200 x 4096 x 12288:
+// 341 us against 519 with 256 x 256, which needs a second round for 16 of its
+// 272 tiles) the choice costs 2% more than the fastest measured one on
+// average.
+Proj choose_wide(int N, int K, int M, int max_split)
+{
+    Proj p;
+    p.N = N;
+    p.K = K;
+    struct Cand {
+        int bm, bn, slots;
+        double lo, full;
+    };
+    static const Cand cands[] = {{320, 256, 256, 80, 131}, {256, 256, 256, 67, 107}, {256, 128, 256, 38, 61},
+                                 {128, 128, 512, 34, 66}};
+    const double fixed = 12;
+    const int smax = std::max(1, std::min(K / 512, max_split > 0 ? max_split : 16));
+    double best = 1e300;
+    int S = 1;
+    for (const Cand &cd : cands) {
+        const long long tiles = (long long)((M + cd.bm - 1) / cd.bm) * ((N + cd.bn - 1) / cd.bn);
+        for (int s = 1; s <= smax; s *= 2) {
+            const long long n = tiles * s, rounds = n / cd.slots, rest = n % cd.slots;
+            const double g = (double)K / s / 4096, x = (double)rest / cd.slots;
+            // the last round; two 128 x 128 workgroups share a CU only once there are more than 256
+            const double c = cd.slots == 512 ? (rest <= 256 ? cd.lo : cd.full) : cd.lo + (cd.full - cd.lo) * x * x;
+            const double t = rounds * (fixed + (cd.full - fixed) * g) + (rest ? fixed + (c - fixed) * g : 0) +
+                             (s - 1) * (double)M * N * 8 / 5e6;
+            if (t < best) {
+                best = t;
+                p.bm = cd.bm;
+                p.bn = cd.bn;
+                S = s;
+            }
+        }
+    }
+    p.Kc = ((K + S - 1) / S + 63) / 64 * 64;
+    p.S = (K + p.Kc - 1) / p.Kc;
+    return p;
+}
+
 GemmShape shape_of(const Proj &p, int M) { return GemmShape{M, p.N, p.K, p.S, p.Kc, mt_for(M), p.bm, p.bn, 0}; }
 
 // Attention chunk: fixed per engine from (B, kv heads, capacity): the
@@ -565,10 +615,18 @@ hipError_t proj(corun_engine *e, const uint16_t *A, int lda, int w, int l, const
 // same fp32 sums, so both paths give the same bits.
 bool gu_fuses(const corun_engine *e, const Proj &pr) { return e->gu_fused && takes_packed(pr) && pr.S == 1; }
 
+// The same for the wide tiles (M > 64), which pair gate and up columns from
+// the row-major weight: no copy needed, any plan without split-K.
+bool gu_fuses_wide(const Proj &pr)
+{
+    return pr.bm >= 128 && pr.bn > 0 && pr.S == 1 && (long long)(pr.N / 2 + 256) * pr.K * 2 < (1ll << 32);
+}
+
 // gate/up of layer l over `rows` rows of A with SwiGLU into act [rows][ffn]
 hipError_t gate_up_swiglu(corun_engine *e, const uint16_t *A, int l, const Proj &pr, int rows, uint16_t *act)
 {
     GemmShape g = shape_of(pr, rows);
+    if (gu_fuses_wide(pr)) return launch_gate_up_wide(A, e->c.hidden, e->w_gu[l], g, act, e->c.ffn, e->st);
     g.pk = 1;
     return launch_gemm_dma(A, e->c.hidden, e->packed[W_GATE_UP][l], g, nullptr, 0, e->c.ffn, e->st, nullptr, act);
 }
@@ -760,7 +818,7 @@ corun_status launch_one(corun_engine *e, int which, int l)
     case CORUN_K_GATE_UP_GEMM:
         if (e->moe) {
             ST_TRY(moe_expert_gate_up(e, decode_moe(e), e->h, l));
-        } else if (gu_fuses(e, p.gu)) {
+        } else if (gu_fuses(e, p.gu) || gu_fuses_wide(p.gu)) {
             HIP_TRY(gate_up_swiglu(e, e->h, l, p.gu, B, e->a));
         } else {
             HIP_TRY(proj(e, e->h, H, W_GATE_UP, l, p.gu, B, e->p_gu, (long long)B * 2 * F, 2 * F));
@@ -770,7 +828,7 @@ corun_status launch_one(corun_engine *e, int which, int l)
         if (e->moe) {
             const int Fe = c.expert_ffn;
             if (!e->egu_fused) HIP_TRY(launch_swiglu(e->moe_gu, 1, 0, B * c.top_k, Fe, e->moe_act, Fe, st));
-        } else if (!gu_fuses(e, p.gu)) {
+        } else if (!gu_fuses(e, p.gu) && !gu_fuses_wide(p.gu)) {
             HIP_TRY(launch_swiglu(e->p_gu, p.gu.S, (long long)B * 2 * F, B, F, e->a, F, st));
         }
         break;
@@ -808,7 +866,7 @@ bool launches(const corun_engine *e, int k)
 {
     if (e->plan.gv) return k != CORUN_K_QKV_POST && k != CORUN_K_SWIGLU && k != CORUN_K_RMSNORM;
     if (k == CORUN_K_QKV_POST) return !e->qkv_in_attn;
-    if (k == CORUN_K_SWIGLU) return e->moe ? !e->egu_fused : !gu_fuses(e, e->plan.gu);
+    if (k == CORUN_K_SWIGLU) return e->moe ? !e->egu_fused : !gu_fuses(e, e->plan.gu) && !gu_fuses_wide(e->plan.gu);
     return true;
 }
 
@@ -943,14 +1001,20 @@ struct PrefillPlan {
 PrefillPlan prefill_plan(const corun_model_cfg &c, int n, bool bi)
 {
     const int H = c.hidden, nqkv = (c.n_heads + 2 * c.n_kv_heads) * c.head_dim, F = c.ffn;
+    // gate/up never splits K above 64 rows: without split-K its epilogue
+    // applies SwiGLU, and neither the fp32 sums nor a SwiGLU kernel remain
+    auto choose = [&](int N, int K, bool whole) {
+        if (n > 128 && K % 64 == 0) return choose_wide(N, K, n, bi || whole ? 1 : 0);
+        return choose_proj(N, K, n, 0, whole && n > 64 ? 1 : 0, 0, bi);
+    };
     PrefillPlan p;
-    p.qkv = choose_proj(nqkv, H, n, 0, 0, 0, bi);
-    p.o = choose_proj(H, c.n_heads * c.head_dim, n, 0, 0, 0, bi);
+    p.qkv = choose(nqkv, H, false);
+    p.o = choose(H, c.n_heads * c.head_dim, false);
     if (c.n_experts == 0) {
-        p.gu = choose_proj(2 * F, H, n, 0, 0, 0, bi);
-        p.down = choose_proj(H, F, n, 0, 0, 0, bi);
+        p.gu = choose(2 * F, H, true);
+        p.down = choose(H, F, false);
     } else {
-        p.router = choose_proj(c.n_experts, H, n, 0, 0, 0, bi);
+        p.router = choose(c.n_experts, H, false);
     }
     return p;
 }
@@ -1487,7 +1551,7 @@ extern "C" corun_status corun_prefill_chunk(corun_engine *e, const int32_t *toke
             if (!e->egu_fused) HIP_TRY(launch_swiglu(e->pf_moe_gu, 1, 0, Lp * c.top_k, Fe, e->pf_moe_act, Fe, st));
             ST_TRY(moe_expert_down(e, pmb, l));
         } else {
-            if (gu_fuses(e, pg)) {
+            if (gu_fuses(e, pg) || gu_fuses_wide(pg)) {
                 HIP_TRY(gate_up_swiglu(e, e->pf_h, l, pg, Lp, e->pf_a));
             } else {
                 HIP_TRY(proj(e, e->pf_h, H, W_GATE_UP, l, pg, Lp, e->pf_part, (long long)Lp * 2 * F, 2 * F));
@@ -1618,7 +1682,7 @@ extern "C" corun_status corun_prefill_batch(corun_engine *e, const int32_t *toke
             if (!e->egu_fused) HIP_TRY(launch_swiglu(e->pf_moe_gu, 1, 0, Lp * c.top_k, Fe, e->pf_moe_act, Fe, st));
             ST_TRY(moe_expert_down(e, pmb, l));
         } else {
-            if (gu_fuses(e, pg)) {
+            if (gu_fuses(e, pg) || gu_fuses_wide(pg)) {
                 HIP_TRY(gate_up_swiglu(e, e->pf_h, l, pg, Lp, e->pf_a));
             } else {
                 HIP_TRY(proj(e, e->pf_h, H, W_GATE_UP, l, pg, Lp, e->pf_part, (long long)Lp * 2 * F, 2 * F));

@@ -106,7 +106,7 @@ struct GemmShape {
     int Kc;         // K elements per split (multiple of 32)
     int mt;         // skinny kernel: 16-row M tiles per wave: 1, 2 or 4
     int bm;         // 0 = skinny kernel; 64, 128, 256 = LDS-tiled kernel with this M tile
-    int bn;         // > 0: pipelined kernel with bm x bn tiles (128 x 128, 256 x 128, 256 x 256)
+    int bn;         // > 0: pipelined kernel with bm x bn tiles
     int pk;         // 1: W is the tile-packed copy (launch_pack_weights); bm 32 or 64, bn 128 only
 };
 // Dispatch on g.bm.
@@ -120,8 +120,9 @@ hipError_t launch_gemm(const uint16_t *A, int lda, const uint16_t *W, const Gemm
 // over grid.y, same output contract as launch_gemm (no argmax epilogue).
 hipError_t launch_gemm_tiled(const uint16_t *A, int lda, const uint16_t *W, const GemmShape &g, int bm, float *out,
                              long long split_stride, int ldo, hipStream_t st, ArgBest *amax = nullptr);
-// Pipelined large-M variant (direct global -> LDS loads, 32x32 MFMA tiles):
-// K and Kc multiples of 64 (32 for bn == 256).
+// Pipelined variant (direct global -> LDS loads, 32x32 MFMA tiles): K and Kc
+// multiples of 64; 32 x 128 and 64 x 128 tiles, and the wide ones 128 x 128,
+// 256 x 128, 256 x 256 and 320 x 256.
 // With act != nullptr (g.pk, S == 1, N % 128 == 0): W is the gate/up-
 // interleaved packed copy of a [2F, K] gate/up weight (launch_pack_weights
 // with interleave) and the kernel writes act[m * ldo + j] = SwiGLU of
@@ -129,6 +130,11 @@ hipError_t launch_gemm_tiled(const uint16_t *A, int lda, const uint16_t *W, cons
 hipError_t launch_gemm_dma(const uint16_t *A, int lda, const uint16_t *W, const GemmShape &g, float *out,
                            long long split_stride, int ldo, hipStream_t st, ArgBest *amax = nullptr,
                            uint16_t *act = nullptr);
+// act[m][j] = SwiGLU of feature j (bf16, ld ldo) from the row-major [2F, K]
+// gate/up weight, the wide tile g.bm x g.bn, no split-K (K % 64 == 0): the
+// bits of launch_proj followed by launch_swiglu.
+hipError_t launch_gate_up_wide(const uint16_t *A, int lda, const uint16_t *W, const GemmShape &g, uint16_t *act, int ldo,
+                               hipStream_t st);
 inline int gemm_col_blocks(int N) { return (N + 63) / 64; }
 // next[r] = best index over the np column-block partials of row r (-1 for padding rows).
 hipError_t launch_argmax_partials(const ArgBest *part, int rows, int np, const uint8_t *valid, int32_t *next,

@@ -20,6 +20,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "kernels.h"
 
@@ -649,9 +650,9 @@ __global__ __launch_bounds__(256) void k_gemm_tiled(const uint16_t *__restrict__
 }
 
 // ---------------------------------------------------------------------------
-// Large-M projection, pipelined: both operands stream global -> LDS with the
-// direct 16-byte LDS loads of gfx950 (no register staging) through a ring of
-// NST stages of BK (32 or 64) K elements: while the matrix cores run stage i
+// Projection of up to 64 rows (and of 16-row expert tiles), pipelined: both
+// operands stream global -> LDS with the direct 16-byte LDS loads of gfx950
+// (no register staging) through a ring of NST stages of BK (64) K elements: while the matrix cores run stage i
 // from registers, stage i + 1 is read from LDS and NST - 1 stages are in
 // flight.  The loads of a stage are the only vector-memory
 // operations of the loop, so "stage i has landed" is a fixed vmcnt: the
@@ -682,10 +683,6 @@ __global__ __launch_bounds__(256) void k_gemm_tiled(const uint16_t *__restrict__
 // are bit-identical to the row-major layout.  At small M, where the kernel
 // streams weights, this is 5-20% faster.
 //
-// Tile order: with several M tiles, workgroups are handed to the eight XCDs
-// in turn, so each XCD gets a contiguous run of tiles, walked in groups of
-// eight M tiles per N tile: the workgroups sharing a weight tile or an
-// activation tile run together on one L2.
 // ---------------------------------------------------------------------------
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
@@ -744,8 +741,9 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_dma(const uint16_t *__restrict
     __shared__ __attribute__((aligned(16))) uint4 ring[NST * STAGE];
 
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int num_m = (M + BM - 1) / BM, num_n = (N + BN - 1) / BN;
-    int t = blockIdx.x, mt, nt;
+    const int num_m = (M + BM - 1) / BM;
+    const int t = blockIdx.x;
+    int mt, nt;
     // expert tiles: grid.y walks the tile slots; rows are the slot's
     // assignments, A row = assignment / row_div, output row = assignment
     int row_end = M, slot_start = 0;
@@ -757,20 +755,9 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_dma(const uint16_t *__restrict
         W += (size_t)et.tiles[3 * sl] * et.w_stride;
         mt = 0;
         nt = t;
-    } else if (num_m == 1) {
-        mt = 0;
-        nt = t;
-    } else {
-        const int T = num_m * num_n;
-        if (T >= 8 && gridDim.y == 1) {
-            const int x = t & 7, j = t >> 3, per = T >> 3, rem = T & 7;
-            t = x * per + min(x, rem) + j;
-        }
-        constexpr int GM = 8;
-        const int group = t / (GM * num_n), first = group * GM, gs = min(num_m - first, GM);
-        const int in = t - group * GM * num_n;
-        mt = first + in % gs;
-        nt = in / gs;
+    } else {                                         // row tiles of one column tile side by side
+        mt = t % num_m;
+        nt = t / num_m;
     }
     const int m0 = mt * BM, n0 = nt * BN;
     const int s = MOE ? 0 : blockIdx.y;
@@ -875,21 +862,6 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_dma(const uint16_t *__restrict
         issue((i + P) % NST, (i + P) * BK);
         read(nxt, (i + 1) % NST);
         mma(cur);
-        // Issue order for one wavefront per SIMD (four wavefronts): the stage
-        // loads, then one fragment read between consecutive products, so the
-        // reads drain while the matrix cores run (lm_head at M = 256: 451 ->
-        // 423 us).  With two wavefronts per SIMD the compiler's own order was
-        // faster (the 256 x 256 tile: 70 against 73 us at M = 256).
-        if constexpr (NW == 4) {
-            constexpr int NRD = (BK / 16) * (FM + FN), NMM = (BK / 16) * FM * FN;
-            __builtin_amdgcn_sched_group_barrier(0x020, OPS, 0);
-#pragma unroll
-            for (int k = 0; k < NRD && k < NMM; ++k) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            }
-            if constexpr (NMM > NRD) __builtin_amdgcn_sched_group_barrier(0x008, NMM - NRD, 0);
-        }
     };
 #pragma unroll
     for (int i = 0; i < P; ++i)
@@ -1000,19 +972,363 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_dma(const uint16_t *__restrict
     }
 }
 
+// ---------------------------------------------------------------------------
+// Wide projection tiles (M > 64: decode from 65 rows up, prefill), pipelined
+// at the granularity of one 16-wide K step.
+//
+// Like k_gemm_dma, both operands stream global -> LDS through a ring of NST
+// stages and every output element is one chain of v_mfma_f32_32x32x16_bf16
+// over K in order, so the tile changes no bit of a result.  What differs is
+// what bounded k_gemm_dma's large tiles (62% of the matrix cores' cycles busy
+// at M = 8192, the rest in instruction issue):
+//  * stages of 64 K elements, so a load instruction covers whole 128-byte
+//    lines (8 rows x 128 bytes, not 16 x 64);
+//  * fragments double-buffered per K step (FM + FN registers' worth, not a
+//    whole stage's), so a 64-wide stage fits the register file;
+//  * a fixed issue order: after each product one fragment read of the next
+//    step, and the stage's loads among the products of the last step of one
+//    stage (the first half) and the first step of the next (the rest), each
+//    one behind its own product, so neither the LDS nor the load path sees a
+//    burst and the matrix cores do not wait for instruction issue;
+//  * loads through a buffer resource with the K offset in a scalar register:
+//    no per-load 64-bit address arithmetic in vector registers;
+//  * one barrier per 64 K elements, before the stage's last K step.
+// Measured (bf16 normal data, same box, old -> new tile): 256 x 256 at
+// M = 8192 over 24576 x 4096 1490 -> 1300 us, 4096 x 12288 691 -> 602,
+// 6144 x 4096 356 -> 312; 256 x 128 1685 -> 1435; 128 x 128 1932 -> 1654.
+// At these rates the card is at its power limit (1.6 GHz under this load; the
+// matrix instruction alone, no memory, reaches 1.77 PFLOP/s on such data).
+//
+// Wavefront tiles are 64 columns wide (FN = 2), as the argmax and SwiGLU
+// epilogues need.
+//
+// SwiGLU epilogue (EPI 1): the tile's W rows are cut into blocks of 128, 64
+// gate rows and the 64 up rows of the same features, and a wavefront's two
+// column fragments are 32 gate and the matching 32 up columns, so each lane
+// holds both sums of a feature and writes its bf16 activation: the fp32
+// [M][2F] sums never reach memory (at M = 32768 over 24576 x 4096 they cost
+// 3.2 GB written and read again).
+//
+// Tile order: with several M tiles, workgroups are handed to the eight XCDs
+// in turn, so each XCD gets a contiguous run of tiles, walked in groups of
+// eight M tiles per N tile: the workgroups sharing a weight tile or an
+// activation tile run together on one L2.
+//
+// MOE: grid.y walks the expert tile slots of up to BM assignments (as in
+// k_gemm_dma).  PKW: W is the tile-packed copy.
+// ---------------------------------------------------------------------------
+enum { WIDE_F32 = 0, WIDE_SWIGLU = 1 };
+
+template <int BM, int BN, int NST, int WGM, int NW, int EPI, bool MOE = false, bool PKW = false>
+__global__ __launch_bounds__(64 * NW) void k_gemm_wide(const uint16_t *__restrict__ A, int lda,
+                                                       const uint16_t *__restrict__ W, int M, int N, int K, int Kc,
+                                                       float *__restrict__ out, long long split_stride, int ldo,
+                                                       ArgBest *__restrict__ amax, uint16_t *__restrict__ act,
+                                                       ExpertTiles et)
+{
+#if defined(__HIP_DEVICE_COMPILE__)   // buffer resources exist in device code only
+    constexpr int BK = 64, C = BK / 8;                // 16-byte chunks per row
+    constexpr int NT = 64 * NW;                       // threads
+    constexpr int WGN = NW / WGM;
+    constexpr int WM = BM / WGM, WN = BN / WGN;
+    constexpr int FM = WM / 32, FN = WN / 32;
+    constexpr int A_OPS = BM * C / NT, W_OPS = BN * C / NT, OPS = A_OPS + W_OPS;
+    constexpr int STAGE = (BM + BN) * C;              // 16-byte units
+    constexpr int NMM = FM * FN, NRD = FM + FN;       // products and fragment reads of a K step
+    constexpr int HALF = OPS / 2;                     // loads of a stage issued in the previous stage's last step
+    static_assert(A_OPS * NT == BM * C && W_OPS * NT == BN * C, "loads cover the tile");
+    static_assert(WN == 64 && NRD <= NMM + 1, "wavefront tiles");
+    static_assert((NST - 2) * OPS + HALF <= 63, "vmcnt range");
+    static_assert(!PKW || BN == 128, "packed weights come in 128 x 64 tiles");
+    __shared__ __attribute__((aligned(16))) uint4 ring[NST * STAGE];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int num_m = (M + BM - 1) / BM, num_n = (N + BN - 1) / BN;
+    int t = blockIdx.x, mt, nt;
+    int row_end = M, slot_start = 0;
+    if constexpr (MOE) {
+        const int sl = blockIdx.y;
+        row_end = et.tiles[3 * sl + 2];
+        if (row_end == 0) return;                     // an unused slot (uniform over the workgroup)
+        slot_start = et.tiles[3 * sl + 1];
+        W += (size_t)et.tiles[3 * sl] * et.w_stride;
+        mt = 0;
+        nt = t;
+    } else if (num_m == 1) {
+        mt = 0;
+        nt = t;
+    } else {
+        const int T = num_m * num_n;
+        if (T >= 8 && gridDim.y == 1) {
+            const int x = t & 7, j = t >> 3, per = T >> 3, rem = T & 7;
+            t = x * per + min(x, rem) + j;
+        }
+        constexpr int GM = 8;
+        const int group = t / (GM * num_n), first = group * GM, gs = min(num_m - first, GM);
+        const int in = t - group * GM * num_n;
+        mt = first + in % gs;
+        nt = in / gs;
+    }
+    const int m0 = mt * BM, n0 = nt * BN;
+    const int s = MOE ? 0 : blockIdx.y;
+    const int kbeg = s * Kc, kend = min(K, kbeg + Kc);
+    const int nk = kend > kbeg ? (kend - kbeg) / BK : 0;
+    const int F = N / 2;                              // features (EPI 1)
+    auto out_row = [&](int row) -> size_t {
+        if constexpr (MOE) return (size_t)et.list[slot_start + row];
+        else return (size_t)row;
+    };
+
+    // per load op j: byte offset of this thread's 16 bytes from the resource's
+    // base; rows past the end load clamped (real) rows and are never stored
+    const uint16_t *abase = A + (MOE ? (size_t)0 : (size_t)m0 * lda) + kbeg;
+    const uint16_t *wbase = W;
+    if constexpr (PKW) wbase += ((size_t)nt * (K / BK) + kbeg / BK) * (BN * BK);
+    else if constexpr (EPI == WIDE_SWIGLU) wbase += (size_t)nt * (BN / 2) * K + kbeg;
+    else wbase += (size_t)n0 * K + kbeg;
+    const auto ra = __builtin_amdgcn_make_buffer_rsrc((void *)abase, 0, 0xFFFFFFFF, 0x00020000);
+    const auto rw = __builtin_amdgcn_make_buffer_rsrc((void *)wbase, 0, 0xFFFFFFFF, 0x00020000);
+    uint32_t ao[A_OPS], wo[W_OPS];
+#pragma unroll
+    for (int j = 0; j < A_OPS; ++j) {
+        const int g = j * NT + tid, r = g / C, c = dma_swz<C>(r, g % C) - r * C;   // the swizzle is an involution
+        uint32_t row;
+        if constexpr (MOE) row = (uint32_t)(et.list[slot_start + min(r, row_end - 1)] / et.row_div);
+        else row = (uint32_t)min(r, M - 1 - m0);
+        ao[j] = (row * (uint32_t)lda + 8 * c) * 2;
+    }
+#pragma unroll
+    for (int j = 0; j < W_OPS; ++j) {
+        const int g = j * NT + tid, r = g / C, c = dma_swz<C>(r, g % C) - r * C;
+        uint32_t row;
+        if constexpr (PKW) {
+            wo[j] = (uint32_t)(r * BK + 8 * c) * 2;
+            continue;
+        } else if constexpr (EPI == WIDE_SWIGLU) {
+            // feature of LDS row r, from the tile's first; up rows F rows on
+            const int f = min(64 * (r >> 7) + (r & 63), F - 1 - nt * (BN / 2));
+            row = (uint32_t)f + ((r & 64) ? (uint32_t)F : 0u);
+        } else {
+            row = (uint32_t)min(r, N - 1 - n0);
+        }
+        wo[j] = (row * (uint32_t)K + 8 * c) * 2;
+    }
+    typedef __attribute__((address_space(3))) void lds_void;
+    auto dma = [&](int q, int slot, int kofs) {       // load op q of the stage at K offset kofs: A's, then W's
+        uint4 *base = ring + slot * STAGE + wave * 64;
+        if (q < A_OPS)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void *)(base + q * NT), 16, ao[q < A_OPS ? q : 0],
+                                                     kofs * 2, 0, 0);
+        else
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void *)(base + BM * C + (q - A_OPS) * NT), 16,
+                                                     wo[q >= A_OPS ? q - A_OPS : 0], PKW ? kofs * 2 * BN : kofs * 2,
+                                                     0, 0);
+    };
+
+    f32x16 acc[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
+
+    const int wn = wave % WGN;
+    const int wm0 = (wave / WGN) * WM, wn0 = wn * WN;
+    const int r32 = lane & 31, h = lane >> 5;
+    // the wavefront's first W row in the tile, and its second fragment's distance
+    const int wrow0 = EPI == WIDE_SWIGLU ? 128 * (wn >> 1) + 32 * (wn & 1) : wn0;
+    constexpr int WFRAG = EPI == WIDE_SWIGLU ? 64 : 32;
+    struct Frags {
+        bf16x8 a[FM], w[FN];
+    };
+    // One K step in its fixed issue order: the products of `cur`; behind
+    // product k (rd) fragment k of K step ks of the stage in rslot, and load
+    // op D0 + k of the stage at kofs into dslot.  Reads follow the order in
+    // which the next step's products need them: a0, w0, w1, a1, ...
+    auto step = [&](const Frags &cur, Frags &nxt, bool rd, int rslot, int ks, int D0, int D1, int dslot, int kofs) {
+        const uint4 *As = ring + rslot * STAGE, *Ws = As + BM * C;
+        const uint4 *ap = As + dma_swz<C>(wm0 + r32, 2 * ks + h), *wp = Ws + dma_swz<C>(wrow0 + r32, 2 * ks + h);
+        const int dper = D1 > D0 ? (D1 - D0 + NMM - 1) / NMM : 0;
+        constexpr int rper = (NRD + NMM - 1) / NMM;
+#pragma unroll
+        for (int k = 0; k < NMM; ++k) {
+            const int i = k / FN, j = k % FN;
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur.a[i], cur.w[j], acc[i][j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (rd)
+#pragma unroll
+                for (int u = 0; u < rper; ++u) {
+                    const int q = k * rper + u;
+                    if (q >= NRD) continue;
+                    if (q == 0) nxt.a[0] = __builtin_bit_cast(bf16x8, ap[0]);
+                    else if (q <= FN) nxt.w[q - 1] = __builtin_bit_cast(bf16x8, wp[(q - 1) * WFRAG * C]);
+                    else nxt.a[q - FN] = __builtin_bit_cast(bf16x8, ap[(q - FN) * 32 * C]);
+                }
+#pragma unroll
+            for (int u = 0; u < dper; ++u)
+                if (D0 + k * dper + u < D1) dma(D0 + k * dper + u, dslot, kofs);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+
+    // stages 0 .. NST - 2 and the first half of stage NST - 1 go out, stage 0 is awaited
+#pragma unroll
+    for (int i = 0; i < NST; ++i)
+        if (i < nk)
+#pragma unroll
+            for (int q = 0; q < (i == NST - 1 ? HALF : OPS); ++q) dma(q, i, i * BK);
+    if (nk >= NST) __builtin_amdgcn_s_waitcnt(vmcnt_imm((NST - 2) * OPS + HALF));
+    else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    lds_barrier();
+    Frags f0, f1;
+    {
+        const uint4 *As = ring, *Ws = As + BM * C;
+#pragma unroll
+        for (int i = 0; i < FM; ++i) f0.a[i] = __builtin_bit_cast(bf16x8, As[dma_swz<C>(wm0 + 32 * i + r32, h)]);
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+            f0.w[j] = __builtin_bit_cast(bf16x8, Ws[dma_swz<C>(wrow0 + WFRAG * j + r32, h)]);
+    }
+    int slot = 0, pslot = NST - 1, i = 0;
+    // Stage i, with stage i + NST still to be begun: the rest of stage
+    // i + NST - 1 goes out in the first K step; the barrier before the last
+    // one follows the wait for this wavefront's LDS reads (so slot i may be
+    // refilled) and for all but the NST - 2 youngest stages (so stage i + 1
+    // may be read).
+    for (; i + NST < nk; ++i) {
+        step(f0, f1, true, slot, 1, HALF, OPS, pslot, (i + NST - 1) * BK);
+        step(f1, f0, true, slot, 2, 0, 0, 0, 0);
+        step(f0, f1, true, slot, 3, 0, 0, 0, 0);
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm((NST - 2) * OPS));
+        __builtin_amdgcn_s_waitcnt(0xC07F);           // lgkmcnt(0)
+        lds_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        const int nslot = slot + 1 == NST ? 0 : slot + 1;
+        step(f1, f0, true, nslot, 0, 0, HALF, slot, (i + NST) * BK);
+        pslot = slot;
+        slot = nslot;
+    }
+    // the last NST stages: nothing further to begin
+    if (i + NST - 1 < nk)
+#pragma unroll
+        for (int q = HALF; q < OPS; ++q) dma(q, pslot, (i + NST - 1) * BK);
+    for (; i < nk; ++i) {
+        step(f0, f1, true, slot, 1, 0, 0, 0, 0);
+        step(f1, f0, true, slot, 2, 0, 0, 0, 0);
+        step(f0, f1, true, slot, 3, 0, 0, 0, 0);
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+        __builtin_amdgcn_s_waitcnt(0xC07F);
+        lds_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        const int nslot = slot + 1 == NST ? 0 : slot + 1;
+        step(f1, f0, i + 1 < nk, nslot, 0, 0, 0, 0, 0);
+        slot = nslot;
+    }
+
+    // lane holds, per 32x32 tile, column r32 and rows 8 (q / 4) + 4 h + q % 4
+    if constexpr (EPI == WIDE_SWIGLU) {
+        const int j = nt * (BN / 2) + 64 * (wn >> 1) + 32 * (wn & 1) + r32;
+        if (j < F)
+#pragma unroll
+            for (int a = 0; a < FM; ++a)
+#pragma unroll
+                for (int q = 0; q < 16; ++q) {
+                    const int row = m0 + wm0 + 32 * a + 8 * (q >> 2) + 4 * h + (q & 3);
+                    if (row < row_end)
+                        act[out_row(row) * ldo + j] = swiglu_bf16(0.f + acc[a][0][q], 0.f + acc[a][1][q]);
+                }
+        return;
+    } else {
+        float *o = out + (size_t)s * split_stride;
+#pragma unroll
+        for (int a = 0; a < FM; ++a)
+#pragma unroll
+            for (int b = 0; b < FN; ++b) {
+                const int col = n0 + wn0 + 32 * b + r32;
+                if (col >= N) continue;
+#pragma unroll
+                for (int q = 0; q < 16; ++q) {
+                    const int row = m0 + wm0 + 32 * a + 8 * (q >> 2) + 4 * h + (q & 3);
+                    if (row < row_end) o[out_row(row) * ldo + col] = acc[a][b][q];
+                }
+            }
+        if (amax != nullptr) {
+            // per row: best (value, column) over this wavefront's 64 columns.
+            // Each 32-row fragment goes through the wavefront's own padded
+            // 32 x 68 float tile in the idle ring (after the last barrier no
+            // wavefront reads it and no load is in flight); lane l scans half
+            // a row, columns in increasing order, then the two halves meet.
+            constexpr int TP = 68;
+            static_assert(NW * 32 * TP * 4 <= NST * STAGE * 16, "argmax staging fits the ring");
+            float *T = reinterpret_cast<float *>(ring) + wave * 32 * TP;
+            const int ncb = (N + 63) / 64;
+            const int rr = lane >> 1, hf = lane & 1;
+#pragma unroll
+            for (int a = 0; a < FM; ++a) {
+#pragma unroll
+                for (int b = 0; b < FN; ++b)
+#pragma unroll
+                    for (int q = 0; q < 16; ++q)
+                        T[(8 * (q >> 2) + 4 * h + (q & 3)) * TP + 32 * b + r32] = acc[a][b][q];
+                float bv = -INFINITY;
+                int bi = 0x7fffffff;
+#pragma unroll
+                for (int i4 = 0; i4 < 8; ++i4) {
+                    const float4 v = *reinterpret_cast<const float4 *>(T + rr * TP + 32 * hf + 4 * i4);
+                    const int col = n0 + wn0 + 32 * hf + 4 * i4;
+                    if (col + 0 < N) better(bv, bi, v.x, col + 0);
+                    if (col + 1 < N) better(bv, bi, v.y, col + 1);
+                    if (col + 2 < N) better(bv, bi, v.z, col + 2);
+                    if (col + 3 < N) better(bv, bi, v.w, col + 3);
+                }
+                const float v2 = __shfl_xor(bv, 1, 64);
+                const int i2 = __shfl_xor(bi, 1, 64);
+                better(bv, bi, v2, i2);
+                const int row = m0 + wm0 + 32 * a + rr;
+                if (hf == 0 && row < M && n0 + wn0 < N) amax[(size_t)row * ncb + (n0 + wn0) / 64] = ArgBest{bv, bi};
+            }
+        }
+    }
+#endif
+}
+
+namespace {
+template <int BM, int BN, int NST, int WGM, int NW, int EPI, bool MOE = false, bool PKW = false>
+hipError_t wide_launch(dim3 grid, hipStream_t st, const uint16_t *A, int lda, const uint16_t *W, int M, int N, int K,
+                       int Kc, float *out, long long split_stride, int ldo, ArgBest *amax, uint16_t *act,
+                       ExpertTiles et)
+{
+    KLAUNCH((k_gemm_wide<BM, BN, NST, WGM, NW, EPI, MOE, PKW>), grid, dim3(64 * NW), 0, st, A, lda, W, M, N, K, Kc, out, split_stride, ldo, amax, act, et);
+    return hipGetLastError();
+}
+
+// The wide tile bm x bn; false if there is none.  128 x 128 tiles that fill
+// at most one round of the 256 CUs take a ring of four stages (loads in
+// flight), more of them two stages, so that two workgroups share a CU (over
+// 24576 x 4096 at M = 8192 1654 against 1868 us).
+template <int EPI, class... Args>
+bool wide_tile(int bm, int bn, hipError_t &e, dim3 grid, Args... args)
+{
+    if (bm == 320 && bn == 256) e = wide_launch<320, 256, 2, 2, 8, EPI>(grid, args...);
+    else if (bm == 256 && bn == 256) e = wide_launch<256, 256, 2, 2, 8, EPI>(grid, args...);
+    else if (bm == 256 && bn == 128) e = wide_launch<256, 128, 3, 2, 4, EPI>(grid, args...);
+    else if (bm == 128 && bn == 128 && grid.x * grid.y <= 256) e = wide_launch<128, 128, 4, 2, 4, EPI>(grid, args...);
+    else if (bm == 128 && bn == 128) e = wide_launch<128, 128, 2, 2, 4, EPI>(grid, args...);
+    else return false;
+    return true;
+}
+}  // namespace
+
 hipError_t launch_gemm_dma(const uint16_t *A, int lda, const uint16_t *W, const GemmShape &g, float *out,
                            long long split_stride, int ldo, hipStream_t st, ArgBest *amax, uint16_t *act)
 {
     // 32 or 64 x 128 (small batches): two wavefronts side by side (32- or
-    // 64-row, 64-column wavefront tiles); 128-column tiles: four wavefronts
-    // (2 x 2, 64-row and 64-column wavefront tiles), 64-element stages;
-    // 256 x 256: eight wavefronts (2 x 4, 128 x 64), two per SIMD, 32-element
-    // stages, three in the ring (96 KB): from M = 256 to 32768 it measured
-    // 1-5% faster than four (gate/up at M = 8192: 1307 against 1378 us).
-    // Every configuration has 64-column wavefront tiles, as the argmax
-    // epilogue needs.
-    const int bk = g.bn == 256 ? 32 : 64;
-    if (g.K % bk != 0 || g.Kc % bk != 0 || g.M <= 0) return hipErrorInvalidValue;
+    // 64-row, 64-column wavefront tiles); above, the wide tiles.  Every
+    // configuration has 64-column wavefront tiles, as the argmax epilogue
+    // needs.
+    if (g.K % 64 != 0 || g.Kc % 64 != 0 || g.M <= 0) return hipErrorInvalidValue;
     const int num_n = (g.N + g.bn - 1) / g.bn;
     const int num_m = (g.M + g.bm - 1) / g.bm;
     dim3 grid(num_m * num_n, g.S);
@@ -1045,18 +1361,29 @@ hipError_t launch_gemm_dma(const uint16_t *A, int lda, const uint16_t *W, const 
     else if (g.bm == 64 && g.bn == 128)
         KLAUNCH((k_gemm_dma<64, 128, 64, 4, 1, 2>), grid, dim3(128), 0, st, A, lda, W, g.M, g.N, g.K, g.Kc,
                            out, split_stride, ldo, amax, nullptr, ExpertTiles{});
-    else if (g.bm == 128 && g.bn == 128)
-        KLAUNCH((k_gemm_dma<128, 128, 64, 4, 2, 4>), grid, dim3(256), 0, st, A, lda, W, g.M, g.N, g.K, g.Kc,
-                           out, split_stride, ldo, amax, nullptr, ExpertTiles{});
-    else if (g.bm == 256 && g.bn == 128)
-        KLAUNCH((k_gemm_dma<256, 128, 64, 3, 2, 4>), grid, dim3(256), 0, st, A, lda, W, g.M, g.N, g.K, g.Kc,
-                           out, split_stride, ldo, amax, nullptr, ExpertTiles{});
-    else if (g.bm == 256 && g.bn == 256)
-        KLAUNCH((k_gemm_dma<256, 256, 32, 3, 2, 8>), grid, dim3(512), 0, st, A, lda, W, g.M, g.N, g.K, g.Kc,
-                           out, split_stride, ldo, amax, nullptr, ExpertTiles{});
-    else
+    else {
+        hipError_t e = hipSuccess;
+        if (wide_tile<WIDE_F32>(g.bm, g.bn, e, grid, st, A, lda, W, g.M, g.N, g.K, g.Kc, out, split_stride, ldo, amax,
+                                (uint16_t *)nullptr, ExpertTiles{}))
+            return e;
         return hipErrorInvalidValue;
+    }
     return hipGetLastError();
+}
+
+hipError_t launch_gate_up_wide(const uint16_t *A, int lda, const uint16_t *W, const GemmShape &g, uint16_t *act, int ldo,
+                               hipStream_t st)
+{
+    // F rows further on, an up row's byte offset from the tile's first gate
+    // row has to fit the load's 32 bits
+    if (g.K % 64 != 0 || g.S != 1 || g.M <= 0 || g.N % 2 != 0 || (long long)(g.N / 2 + 256) * g.K * 2 >= (1ll << 32))
+        return hipErrorInvalidValue;
+    const dim3 grid(((g.M + g.bm - 1) / g.bm) * ((g.N + g.bn - 1) / g.bn), 1);
+    hipError_t e = hipSuccess;
+    if (wide_tile<WIDE_SWIGLU>(g.bm, g.bn, e, grid, st, A, lda, W, g.M, g.N, g.K, g.K, (float *)nullptr, 0ll, ldo,
+                               (ArgBest *)nullptr, act, ExpertTiles{}))
+        return e;
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_gemm_tiled(const uint16_t *A, int lda, const uint16_t *W, const GemmShape &g, int bm, float *out,
