@@ -359,7 +359,7 @@ struct corun_engine {
     uint16_t *moe_act = nullptr;
     // and prefill
     float *pf_moe_w = nullptr, *pf_moe_gu = nullptr, *pf_moe_y = nullptr;
-    int32_t *pf_moe_sel = nullptr, *pf_moe_list = nullptr, *pf_moe_tiles = nullptr;
+    int32_t *pf_moe_sel = nullptr, *pf_moe_list = nullptr, *pf_moe_tiles = nullptr, *pf_moe_count = nullptr;
     uint16_t *pf_moe_act = nullptr;
     // routing record (record_routing): [L][B] decode rows, [L][max_prefill_len]
     // prefill rows; pf_trace_rows = the rows of the last prefill call
@@ -637,7 +637,8 @@ struct MoeBufs {
     float *router_part, *w, *gu, *y;
     int32_t *sel, *list, *tiles;
     uint16_t *act;
-    int slots;
+    int32_t *count;      // dispatch scratch, or nullptr
+    int tile_rows, slots;
     // routing record (corun_options.record_routing): layer l's choice and
     // router logits at sel_trace + l rows top_k and logit_trace + l rows E
     int32_t *sel_trace = nullptr;
@@ -652,7 +653,8 @@ corun_status moe_router(corun_engine *e, const MoeBufs &m, const uint16_t *h, in
     float *lt_l = m.logit_trace ? m.logit_trace + (size_t)l * rows * c.n_experts : nullptr;
     HIP_TRY(launch_moe_route(m.router_part, pr.S, (long long)rows * c.n_experts, rows, c.n_experts, c.top_k, m.valid,
                              m.sel, m.w, e->st, st_l, lt_l));
-    HIP_TRY(launch_moe_dispatch(m.sel, rows * c.top_k, c.n_experts, m.slots, m.list, m.tiles, e->st));
+    HIP_TRY(launch_moe_dispatch(m.sel, rows * c.top_k, c.n_experts, m.slots, m.tile_rows, m.list, m.tiles, m.count,
+                                e->st));
     return CORUN_OK;
 }
 
@@ -666,11 +668,11 @@ corun_status moe_expert_gate_up(corun_engine *e, const MoeBufs &m, const uint16_
     const std::vector<const uint16_t *> &pk = e->packed[W_EXP_GATE_UP];
     if (!pk.empty())
         HIP_TRY(launch_moe_gemm_dma(h, H, c.top_k, pk[l], (long long)packed_weight_elems(2 * Fe, H), true, 2 * Fe, H,
-                                    m.list, m.tiles, m.slots, m.gu, e->egu_fused ? m.act : nullptr,
+                                    m.list, m.tiles, m.slots, m.tile_rows, m.gu, e->egu_fused ? m.act : nullptr,
                                     e->egu_fused ? Fe : 2 * Fe, e->st));
     else
         HIP_TRY(launch_moe_gemm_dma(h, H, c.top_k, e->w_egu[l], (long long)2 * Fe * H, false, 2 * Fe, H, m.list,
-                                    m.tiles, m.slots, m.gu, nullptr, 2 * Fe, e->st));
+                                    m.tiles, m.slots, m.tile_rows, m.gu, nullptr, 2 * Fe, e->st));
     return CORUN_OK;
 }
 
@@ -683,20 +685,46 @@ corun_status moe_expert_down(corun_engine *e, const MoeBufs &m, int l)
     const std::vector<const uint16_t *> &pk = e->packed[W_EXP_DOWN];
     if (!pk.empty())
         HIP_TRY(launch_moe_gemm_dma(m.act, Fe, 1, pk[l], (long long)packed_weight_elems(H, Fe), true, H, Fe, m.list,
-                                    m.tiles, m.slots, m.y, nullptr, H, e->st));
+                                    m.tiles, m.slots, m.tile_rows, m.y, nullptr, H, e->st));
     else if (Fe % 64 == 0)
         HIP_TRY(launch_moe_gemm_dma(m.act, Fe, 1, e->w_edown[l], (long long)H * Fe, false, H, Fe, m.list, m.tiles,
-                                    m.slots, m.y, nullptr, H, e->st));
+                                    m.slots, m.tile_rows, m.y, nullptr, H, e->st));
     else
         HIP_TRY(launch_moe_gemm(m.act, Fe, 1, e->w_edown[l], (long long)H * Fe, H, Fe, m.list, m.tiles, m.slots, m.y,
                                 H, e->st));
     return CORUN_OK;
 }
 
+// Rows per expert tile of a prefill over `rows` rows: a tile's weights are
+// streamed once per tile, so tiles grow with the rows an expert gets on
+// average (rows top_k / E).  Each output is one K chain whatever the tile, so
+// the choice moves no bit.  Measured on two layers of the 128-expert top-8
+// model, us per prefill with 16 / 64 / 128 / 256 rows: 100 tokens 619 / 619 /
+// 651 / 741, 200 741 / 698 / 710 / 840, 500 990 / 849 / 840 / 990, 1200 1573 /
+// 1159 / 1103 / 1255, 3000 3065 / 1950 / 1808 / 1967, 8000 7909 / 4765 / 4401 /
+// 4626.
+int moe_tile_rows(const corun_engine *e, int rows)
+{
+    const corun_model_cfg &c = e->c;
+    if (e->packed[W_EXP_GATE_UP].empty() || e->packed[W_EXP_DOWN].empty()) return 16;
+    if ((long long)rows * c.top_k * std::max(c.hidden, c.expert_ffn) * 2 >= (1ll << 32)) return 16;   // 32-bit row offsets
+    const double per = (double)rows * c.top_k / c.n_experts;
+    return per <= 8 ? 16 : per <= 24 ? 64 : 128;
+}
+
+MoeBufs prefill_moe(corun_engine *e, int rows)
+{
+    const corun_model_cfg &c = e->c;
+    const int T = e->moe ? moe_tile_rows(e, rows) : 16;
+    return MoeBufs{nullptr,          e->pf_part,      e->pf_moe_w,     e->pf_moe_gu, e->pf_moe_y,
+                   e->pf_moe_sel,    e->pf_moe_list,  e->pf_moe_tiles, e->pf_moe_act, e->pf_moe_count, T,
+                   e->moe ? c.n_experts + (rows * c.top_k + T - 1) / T : 0, e->rt_pf_sel, e->rt_pf_logit};
+}
+
 MoeBufs decode_moe(corun_engine *e)
 {
     return MoeBufs{e->d_valid, e->p_router, e->moe_w,     e->moe_gu,         e->moe_y,         e->moe_sel,
-                   e->moe_list, e->moe_tiles, e->moe_act, e->plan.moe_slots, e->rt_sel, e->rt_logit};
+                   e->moe_list, e->moe_tiles, e->moe_act, nullptr, 16, e->plan.moe_slots, e->rt_sel, e->rt_logit};
 }
 
 // The residual fold that opens layer l (l = n_layers: the final norm): the
@@ -1081,6 +1109,7 @@ static corun_status alloc_prefill(corun_engine *e)
         cv.take(&e->pf_moe_list, na);
         cv.take(&e->pf_moe_tiles, (size_t)3 * (c.n_experts + (na + 15) / 16));
         cv.take(&e->pf_moe_act, na * Fe);
+        cv.take(&e->pf_moe_count, (na + 1023) / 1024 * c.n_experts);
         if (e->opt.record_routing) {
             cv.take(&e->rt_pf_sel, (size_t)c.n_layers * na);
             cv.take(&e->rt_pf_logit, (size_t)c.n_layers * L * c.n_experts);
@@ -1102,7 +1131,7 @@ static corun_status alloc_prefill(corun_engine *e)
     if (e->moe) {
         rebase(e->pf_moe_w, e->pws); rebase(e->pf_moe_gu, e->pws); rebase(e->pf_moe_y, e->pws);
         rebase(e->pf_moe_sel, e->pws); rebase(e->pf_moe_list, e->pws); rebase(e->pf_moe_tiles, e->pws);
-        rebase(e->pf_moe_act, e->pws);
+        rebase(e->pf_moe_act, e->pws); rebase(e->pf_moe_count, e->pws);
         if (e->opt.record_routing) {
             rebase(e->rt_pf_sel, e->pws);
             rebase(e->rt_pf_logit, e->pws);
@@ -1526,10 +1555,7 @@ extern "C" corun_status corun_prefill_chunk(corun_engine *e, const int32_t *toke
     const Proj &pq = pp.qkv, &po = pp.o, &pg = pp.gu, &pd = pp.down, &pr = pp.router;
     const Proj pl = choose_proj(c.vocab, H, 1, 1, 0, 0, bi);
     const int dense_S = e->moe ? 0 : pd.S;
-    const MoeBufs pmb{nullptr,         e->pf_part,       e->pf_moe_w,   e->pf_moe_gu,
-                      e->pf_moe_y,     e->pf_moe_sel,    e->pf_moe_list, e->pf_moe_tiles,
-                      e->pf_moe_act,   e->moe ? c.n_experts + (Lp * c.top_k + 15) / 16 : 0,
-                      e->rt_pf_sel,    e->rt_pf_logit};
+    const MoeBufs pmb = prefill_moe(e, Lp);
     e->pf_trace_rows = Lp;
 
     HIP_TRY(hipMemcpyAsync(e->pf_tok, tokens, sizeof(int32_t) * Lp, hipMemcpyHostToDevice, st));
@@ -1653,10 +1679,7 @@ extern "C" corun_status corun_prefill_batch(corun_engine *e, const int32_t *toke
     const Proj &pq = pp.qkv, &po = pp.o, &pg = pp.gu, &pd = pp.down, &pr = pp.router;
     const Proj pl = choose_proj(c.vocab, H, n, 1, 0, 0, true);
     const int dense_S = e->moe ? 0 : pd.S;
-    const MoeBufs pmb{nullptr,         e->pf_part,       e->pf_moe_w,   e->pf_moe_gu,
-                      e->pf_moe_y,     e->pf_moe_sel,    e->pf_moe_list, e->pf_moe_tiles,
-                      e->pf_moe_act,   e->moe ? c.n_experts + (Lp * c.top_k + 15) / 16 : 0,
-                      e->rt_pf_sel,    e->rt_pf_logit};
+    const MoeBufs pmb = prefill_moe(e, Lp);
     e->pf_trace_rows = Lp;
 
     HIP_TRY(hipMemcpyAsync(e->pf_tok, tokens, sizeof(int32_t) * Lp, hipMemcpyHostToDevice, st));

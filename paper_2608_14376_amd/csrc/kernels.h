@@ -53,23 +53,28 @@ hipError_t launch_moe_route(const float *part, int S, long long part_stride, int
                             const uint8_t *valid, int32_t *sel, float *wsel, hipStream_t st,
                             int32_t *sel_trace = nullptr, float *logit_trace = nullptr);
 // Deterministic dispatch of the n_assign = rows * top_k assignments into the
-// fixed pool of n_slots 16-row tiles: list (expert-major, increasing
-// assignment) and tiles[slot] = {expert, first list index, count}.
-hipError_t launch_moe_dispatch(const int32_t *sel, int n_assign, int E, int n_slots, int32_t *list, int32_t *tiles,
-                               hipStream_t st);
+// fixed pool of n_slots tiles of tile_rows rows (at least E + n_assign /
+// tile_rows of them): list (expert-major, increasing assignment) and
+// tiles[slot] = {expert, first list index, count}.  With count (scratch,
+// ceil(n_assign / 1024) x E) many assignments take a two-launch form; the
+// results are the same.
+hipError_t launch_moe_dispatch(const int32_t *sel, int n_assign, int E, int n_slots, int tile_rows, int32_t *list,
+                               int32_t *tiles, int32_t *count, hipStream_t st);
 // out[a][n] = sum_k A[a / row_div][k] W_e[n][k] for every listed assignment a
 // of expert e (W_e = W + e * w_expert_stride), one launch over all tile slots.
 hipError_t launch_moe_gemm(const uint16_t *A, int lda, int row_div, const uint16_t *W, long long w_expert_stride, int N,
                            int K, const int32_t *list, const int32_t *tiles, int n_slots, float *out, int ldo,
                            hipStream_t st);
-// The same product on the pipelined kernel (K % 64 == 0): one 32 x 128 tile
-// per (128 columns, tile slot), weights row-major per expert or tile-packed
-// per expert (packed; w_expert_stride in elements of the packed copy).
+// The same product on the pipelined kernels (K % 64 == 0), weights row-major
+// per expert or tile-packed per expert (packed; w_expert_stride in elements of
+// the packed copy), one tile per (128 columns, tile slot): 32 x 128 for
+// tile_rows = 16; 64, 128 or 256 (packed only) the wide tile of that many
+// rows.  Every output is one K chain whatever the tile: the same bits.
 // With act (packed gate/up-interleaved copies, N % 128 == 0) the epilogue
 // writes act[a][j] = SwiGLU of feature j (bf16, ld ldo) instead of out.
 hipError_t launch_moe_gemm_dma(const uint16_t *A, int lda, int row_div, const uint16_t *W, long long w_expert_stride,
                                bool packed, int N, int K, const int32_t *list, const int32_t *tiles, int n_slots,
-                               float *out, uint16_t *act, int ldo, hipStream_t st);
+                               int tile_rows, float *out, uint16_t *act, int ldo, hipStream_t st);
 
 // Projection partials: out[s][m][n] = sum_{k in chunk s} A[m][k] W[n][k]
 // for m < M_store (bf16 MFMA, fp32 accumulate).  A has lda columns and at

@@ -2766,8 +2766,8 @@ hipError_t launch_moe_route(const float *part, int S, long long part_stride, int
 // its bit plus what earlier chunks placed.  Every output is a function of
 // sel alone.
 __global__ __launch_bounds__(1024) void k_moe_dispatch(const int32_t *__restrict__ sel, int n_assign, int E,
-                                                       int n_slots, int32_t *__restrict__ list,
-                                                       int32_t *__restrict__ tiles)
+                                                       int n_slots, int tile_rows,
+                                                       int32_t *__restrict__ list, int32_t *__restrict__ tiles)
 {
     __shared__ int cnt[256], base[256], toff[257], scan_v[256], scan_w[256];
     __shared__ uint32_t mask[256 * 32];
@@ -2780,7 +2780,7 @@ __global__ __launch_bounds__(1024) void k_moe_dispatch(const int32_t *__restrict
     }
     __syncthreads();
     // exclusive scans of counts and tile counts over the experts (Hillis-Steele)
-    const int c = tid < E ? cnt[tid] : 0, nt = (c + 15) / 16;
+    const int c = tid < E ? cnt[tid] : 0, nt = (c + tile_rows - 1) / tile_rows;
     int v = c, w = nt;
     for (int off = 1; off < 256; off <<= 1) {
         if (tid < 256) {
@@ -2804,8 +2804,8 @@ __global__ __launch_bounds__(1024) void k_moe_dispatch(const int32_t *__restrict
         for (int j = 0; j < nt; ++j) {
             const int slot = toff[tid] + j;
             tiles[3 * slot + 0] = tid;
-            tiles[3 * slot + 1] = base[tid] + 16 * j;
-            tiles[3 * slot + 2] = min(16, c - 16 * j);
+            tiles[3 * slot + 1] = base[tid] + tile_rows * j;
+            tiles[3 * slot + 2] = min(tile_rows, c - tile_rows * j);
         }
     for (int slot = toff[256] + tid; slot < n_slots; slot += 1024) {
         tiles[3 * slot + 0] = 0;
@@ -2834,11 +2834,108 @@ __global__ __launch_bounds__(1024) void k_moe_dispatch(const int32_t *__restrict
     }
 }
 
-hipError_t launch_moe_dispatch(const int32_t *sel, int n_assign, int E, int n_slots, int32_t *list, int32_t *tiles,
-                               hipStream_t st)
+// The same dispatch for many assignments, over blocks of 1024 in two
+// launches: k_moe_count writes each block's count per expert, then every
+// block of k_moe_place sums the counts of all blocks (expert totals, and its
+// own offset within each expert: what earlier blocks placed) and places its
+// 1024 assignments by the same mask popcounts; block 0 also writes the tiles.
+// The lists and tiles are those of k_moe_dispatch.  One workgroup walking
+// 24000 assignments took 83 us, the two launches 12.
+__global__ __launch_bounds__(1024) void k_moe_count(const int32_t *__restrict__ sel, int n_assign, int E,
+                                                    int32_t *__restrict__ count)
 {
-    if (E > 256) return hipErrorInvalidValue;
-    KLAUNCH(k_moe_dispatch, dim3(1), dim3(1024), 0, st, sel, n_assign, E, n_slots, list, tiles);
+    __shared__ int cnt[256];
+    const int tid = threadIdx.x;
+    if (tid < 256) cnt[tid] = 0;
+    __syncthreads();
+    const int a = blockIdx.x * 1024 + tid;
+    const int e = a < n_assign ? sel[a] : -1;
+    if (e >= 0) atomicAdd(&cnt[e], 1);
+    __syncthreads();
+    if (tid < E) count[(size_t)blockIdx.x * E + tid] = cnt[tid];
+}
+
+__global__ __launch_bounds__(1024) void k_moe_place(const int32_t *__restrict__ sel, int n_assign, int E, int n_slots,
+                                                    int tile_rows, const int32_t *__restrict__ count,
+                                                    int32_t *__restrict__ list, int32_t *__restrict__ tiles)
+{
+    __shared__ int part_all[1024], part_mine[1024], base[256], scan_v[256], scan_w[256], total_tiles;
+    __shared__ uint32_t mask[256 * 32];
+    const int tid = threadIdx.x, nb = gridDim.x, blk = blockIdx.x;
+    for (int i = tid; i < 256 * 32; i += 1024) mask[i] = 0u;
+    // four threads per expert, each a quarter of the blocks
+    {
+        const int e = tid & 255, quarter = tid >> 8;
+        int all = 0, mine = 0;
+        if (e < E)
+            for (int b = quarter; b < nb; b += 4) {
+                const int n = count[(size_t)b * E + e];
+                all += n;
+                if (b < blk) mine += n;
+            }
+        part_all[tid] = all;
+        part_mine[tid] = mine;
+    }
+    __syncthreads();
+    int c = 0, mine = 0;
+    if (tid < 256)
+        for (int k = 0; k < 4; ++k) {
+            c += part_all[tid + 256 * k];
+            mine += part_mine[tid + 256 * k];
+        }
+    const int nt = (c + tile_rows - 1) / tile_rows;
+    int v = c, w = nt;
+    for (int off = 1; off < 256; off <<= 1) {
+        if (tid < 256) {
+            scan_v[tid] = v;
+            scan_w[tid] = w;
+        }
+        __syncthreads();
+        if (tid < 256 && tid >= off) {
+            v += scan_v[tid - off];
+            w += scan_w[tid - off];
+        }
+        __syncthreads();
+    }
+    if (tid < 256) base[tid] = v - c + mine;
+    if (tid == 255) total_tiles = w;
+    __syncthreads();
+    if (blk == 0) {
+        if (tid < E)
+            for (int j = 0; j < nt; ++j) {
+                const int slot = w - nt + j;
+                tiles[3 * slot + 0] = tid;
+                tiles[3 * slot + 1] = v - c + tile_rows * j;
+                tiles[3 * slot + 2] = min(tile_rows, c - tile_rows * j);
+            }
+        for (int slot = total_tiles + tid; slot < n_slots; slot += 1024) {
+            tiles[3 * slot + 0] = 0;
+            tiles[3 * slot + 1] = 0;
+            tiles[3 * slot + 2] = 0;
+        }
+    }
+    const int a = blk * 1024 + tid;
+    const int e = a < n_assign ? sel[a] : -1;
+    if (e >= 0) atomicOr(&mask[e * 32 + (tid >> 5)], 1u << (tid & 31));
+    __syncthreads();
+    if (e >= 0) {
+        int rank = __popc(mask[e * 32 + (tid >> 5)] & ((1u << (tid & 31)) - 1u));
+        for (int j = 0; j < (tid >> 5); ++j) rank += __popc(mask[e * 32 + j]);
+        list[base[e] + rank] = a;
+    }
+}
+
+hipError_t launch_moe_dispatch(const int32_t *sel, int n_assign, int E, int n_slots, int tile_rows, int32_t *list,
+                               int32_t *tiles, int32_t *count, hipStream_t st)
+{
+    if (E > 256 || tile_rows < 1) return hipErrorInvalidValue;
+    if (n_assign > 2048 && count != nullptr) {   // below, the one launch is as fast (two blocks' walk: about 8 us)
+        const int nb = (n_assign + 1023) / 1024;
+        KLAUNCH(k_moe_count, dim3(nb), dim3(1024), 0, st, sel, n_assign, E, count);
+        KLAUNCH(k_moe_place, dim3(nb), dim3(1024), 0, st, sel, n_assign, E, n_slots, tile_rows, count, list, tiles);
+        return hipGetLastError();
+    }
+    KLAUNCH(k_moe_dispatch, dim3(1), dim3(1024), 0, st, sel, n_assign, E, n_slots, tile_rows, list, tiles);
     return hipGetLastError();
 }
 
@@ -2936,11 +3033,32 @@ hipError_t launch_moe_gemm(const uint16_t *A, int lda, int row_div, const uint16
 
 hipError_t launch_moe_gemm_dma(const uint16_t *A, int lda, int row_div, const uint16_t *W, long long w_expert_stride,
                                bool packed, int N, int K, const int32_t *list, const int32_t *tiles, int n_slots,
-                               float *out, uint16_t *act, int ldo, hipStream_t st)
+                               int tile_rows, float *out, uint16_t *act, int ldo, hipStream_t st)
 {
     if (K % 64 != 0 || N <= 0 || (act != nullptr && (!packed || N % 128 != 0))) return hipErrorInvalidValue;
     const ExpertTiles et{list, tiles, row_div, w_expert_stride};
     const dim3 grid((N + 127) / 128, n_slots);
+    if (tile_rows > 16) {
+        if (!packed) return hipErrorInvalidValue;
+        const auto go = [&](auto epi) {
+            constexpr int EPI = decltype(epi)::value;
+            switch (tile_rows) {
+            case 64:
+                return wide_launch<64, 128, 2, 1, 2, EPI, true, true>(grid, st, A, lda, W, 64, N, K, K, out, 0, ldo,
+                                                                      nullptr, act, et);
+            case 128:
+                return wide_launch<128, 128, 2, 2, 4, EPI, true, true>(grid, st, A, lda, W, 128, N, K, K, out, 0, ldo,
+                                                                       nullptr, act, et);
+            case 256:
+                return wide_launch<256, 128, 3, 2, 4, EPI, true, true>(grid, st, A, lda, W, 256, N, K, K, out, 0, ldo,
+                                                                       nullptr, act, et);
+            default:
+                return hipErrorInvalidValue;
+            }
+        };
+        return act != nullptr ? go(std::integral_constant<int, WIDE_SWIGLU>{})
+                              : go(std::integral_constant<int, WIDE_F32>{});
+    }
     if (act != nullptr)
         KLAUNCH((k_gemm_dma<32, 128, 64, 4, 1, 2, true, true, true>), grid, dim3(128), 0, st, A, lda, W, 16,
                            N, K, K, nullptr, 0, ldo, nullptr, act, et);
