@@ -406,6 +406,7 @@ struct corun_engine {
     int32_t *d_spos = nullptr, *d_stok = nullptr;
     uint64_t *d_sseed = nullptr;
     float *d_stemp = nullptr, *d_slp = nullptr;
+    SamplePart *d_sparts = nullptr;
     char *h_samp = nullptr;
 
     hipGraph_t graph = nullptr;
@@ -1344,6 +1345,7 @@ extern "C" corun_status corun_engine_create(const corun_model_cfg *cfg, const co
     cv.take(&e->d_sseed, (size_t)B);
     cv.take(&e->d_stemp, (size_t)B);
     cv.take(&e->d_slp, (size_t)B);
+    cv.take(&e->d_sparts, sample_scratch_parts(B, cfg->vocab));
     cv.take(&e->h, (size_t)p.Mp * H);
     cv.take(&e->q, (size_t)B * nq * d);
     cv.take(&e->o, (size_t)p.Mp * nq * d);
@@ -1359,7 +1361,7 @@ extern "C" corun_status corun_engine_create(const corun_model_cfg *cfg, const co
     rebase(e->logits, e->ws); rebase(e->p_lm, e->ws); rebase(e->amax, e->ws); rebase(e->h, e->ws); rebase(e->q, e->ws); rebase(e->o, e->ws); rebase(e->a, e->ws);
     rebase(e->rope, e->ws);
     rebase(e->d_svalid, e->ws); rebase(e->d_spos, e->ws); rebase(e->d_stok, e->ws); rebase(e->d_sseed, e->ws);
-    rebase(e->d_stemp, e->ws); rebase(e->d_slp, e->ws);
+    rebase(e->d_stemp, e->ws); rebase(e->d_slp, e->ws); rebase(e->d_sparts, e->ws);
     if (moe) {
         rebase(e->p_router, e->ws); rebase(e->moe_w, e->ws); rebase(e->moe_gu, e->ws); rebase(e->moe_y, e->ws);
         rebase(e->moe_sel, e->ws); rebase(e->moe_list, e->ws); rebase(e->moe_tiles, e->ws); rebase(e->moe_act, e->ws);
@@ -1804,7 +1806,7 @@ extern "C" corun_status corun_sample(corun_engine *e, const float *logits_dev, i
     HIP_TRY(hipMemcpyAsync(e->d_stemp, htemp, sizeof(float) * rows, hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(e->d_svalid, hval, rows, hipMemcpyHostToDevice, st));
     HIP_TRY(launch_sample(logits_dev, ld, rows, e->c.vocab, e->d_svalid, e->d_spos, e->d_sseed, e->d_stemp,
-                          e->d_stok, e->d_slp, st));
+                          e->d_stok, e->d_slp, e->d_sparts, st));
     HIP_TRY(hipMemcpyAsync(htok, e->d_stok, sizeof(int32_t) * rows, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipMemcpyAsync(hlp, e->d_slp, sizeof(float) * rows, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));

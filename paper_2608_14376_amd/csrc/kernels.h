@@ -178,9 +178,18 @@ hipError_t launch_attn_merge(const float *ws, int rows, const uint8_t *valid, co
 // Seeded sampling of rows of fp32 logits (row stride ld): token[r] =
 // argmax_v (l_v / temp[r] + g_v) with g_v from Philox4x32-10 keyed by seed[r],
 // counter (pos[r], v, 0, 0); greedy where temp[r] <= 0; logprob[r] of the
-// chosen token; padding rows get -1 / 0.
+// chosen token; padding rows get -1 / 0.  scratch: sample_scratch_parts(rows,
+// V) entries, or nullptr (one workgroup per row, no scratch); the same bits
+// either way.
+constexpr int SAMPLE_MAX_PARTS = 512;
+struct SamplePart {
+    double z, M, S;   // best score, largest logit / T, sum exp(l / T - M)
+    int i, pad;       // the best score's column
+};
+size_t sample_scratch_parts(int rows, int V);
 hipError_t launch_sample(const float *logits, long long ld, int rows, int V, const uint8_t *valid, const int32_t *pos,
-                         const uint64_t *seed, const float *temp, int32_t *token, float *logprob, hipStream_t st);
+                         const uint64_t *seed, const float *temp, int32_t *token, float *logprob, SamplePart *scratch,
+                         hipStream_t st);
 
 // Causal attention of the isolated prefill: q (bf16 [n][nq d], row i = query
 // position p0 + i) against keys 0..t of `slot` for query position t, o (bf16

@@ -3421,9 +3421,28 @@ hipError_t launch_prefill_attn(const uint16_t *q, int n, int p0, int nq, int nkv
 // a function of (seed, t, v) only: no state is consumed, so padding rows and
 // co-runners cannot shift a request's stream.  T <= 0 is greedy.  Decision
 // and log-probability (of the chosen token under softmax(l / T), softmax(l)
-// when greedy) in fp64; reductions in a fixed tree over 1024 threads:
-// sequential per thread over its columns, then the 64-lane butterfly, then
-// the 16 wavefronts in order.
+// when greedy) in fp64.
+//
+// The row is cut into parts of sample_part_size(V) columns (a function of V
+// alone), a workgroup of 256 threads per part: its best score, its largest
+// logit M_p and S_p = sum exp(l / T - M_p) in a fixed tree (sequential per
+// thread, 64-lane butterfly, the four wavefronts in order).  The merge takes
+// the best score, M = max M_p and sum_p S_p exp(M_p - M) in part order.
+//
+// What bounds it is arithmetic, so the parts do less of it than one workgroup
+// per row evaluating everything did (162 live rows of 151936 on 162 of the
+// 256 CUs: 388 us; parts and merge: 124 us):
+//  * a column's score needs two fp64 logarithms only if it can win.  With
+//    s = 1 - u, -ln u >= s, so g <= -ln s and the score is below b (the
+//    wavefront's best so far) for certain once s > exp(l / T - b).  The test
+//    is made in fp32 with s rounded down to 26 bits and a margin of 1e-3,
+//    far above its own error; a NaN or a tie never rejects.  A few columns of
+//    each wavefront's thousands pass.
+//  * l / T is a product with the fp64 reciprocal and one correction step
+//    (q' = q + (l - q T) / T, correctly rounded: Markstein, IBM J. Res. Dev.
+//    34, 1990) instead of a division per column and pass.
+//  * Philox's products are 32 x 32 -> 64 bit multiplies (one instruction for
+//    both halves).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void philox4x32_10(uint32_t c[4], uint32_t k0, uint32_t k1)
 {
@@ -3435,23 +3454,20 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c[4], uint32_t k0, uint32
             k0 += 0x9E3779B9u;
             k1 += 0xBB67AE85u;
         }
-        const uint32_t lo0 = 0xD2511F53u * c[0], hi0 = __umulhi(0xD2511F53u, c[0]);
-        const uint32_t lo1 = 0xCD9E8D57u * c[2], hi1 = __umulhi(0xCD9E8D57u, c[2]);
-        const uint32_t n0 = hi1 ^ c[1] ^ k0, n2 = hi0 ^ c[3] ^ k1;
+        const uint64_t p0 = (uint64_t)0xD2511F53u * c[0], p1 = (uint64_t)0xCD9E8D57u * c[2];
+        const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c[1] ^ k0, n2 = (uint32_t)(p0 >> 32) ^ c[3] ^ k1;
         c[0] = n0;
-        c[1] = lo1;
+        c[1] = (uint32_t)p1;
         c[2] = n2;
-        c[3] = lo0;
+        c[3] = (uint32_t)p0;
     }
 }
 
-__device__ __forceinline__ double gumbel_noise(uint32_t k0, uint32_t k1, int t, int v)
+__device__ __forceinline__ double gumbel_noise(uint32_t w0, uint32_t w1)
 {
-    uint32_t c[4] = {(uint32_t)t, (uint32_t)v, 0u, 0u};
-    philox4x32_10(c, k0, k1);
-    // u strictly inside (0, 1): ((c0 >> 6) 2^26 + (c1 >> 6) + 1/2) 2^-52, in
+    // u strictly inside (0, 1): ((w0 >> 6) 2^26 + (w1 >> 6) + 1/2) 2^-52, in
     // [2^-53, 1 - 2^-53], every value exact (53-bit integer part)
-    const double u = ((double)(c[0] >> 6) * 67108864.0 + (double)(c[1] >> 6) + 0.5) * (1.0 / 4503599627370496.0);
+    const double u = ((double)(w0 >> 6) * 67108864.0 + (double)(w1 >> 6) + 0.5) * (1.0 / 4503599627370496.0);
     return -log(-log(u));
 }
 
@@ -3463,74 +3479,200 @@ __device__ __forceinline__ void better_d(double &v, int &i, double v2, int i2)
     }
 }
 
-__global__ __launch_bounds__(1024) void k_sample(const float *__restrict__ logits, long long ld, int V,
-                                                 const uint8_t *__restrict__ valid, const int32_t *__restrict__ pos,
-                                                 const uint64_t *__restrict__ seed, const float *__restrict__ temp,
-                                                 int32_t *__restrict__ token, float *__restrict__ logprob)
+// l / T, correctly rounded, from T's rounded reciprocal; infinities and NaN
+// pass through the product alone
+__device__ __forceinline__ double div_by(float lf, double T, double rT)
 {
-    const int r = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (!valid[r]) {
-        if (tid == 0) {
-            token[r] = -1;
-            logprob[r] = 0.f;
-        }
-        return;
-    }
-    __shared__ double sz[16], sm[16];
-    __shared__ int si[16];
-    const float *l = logits + (size_t)r * ld;
-    const float tf = temp[r];
+    const double l = (double)lf, q = l * rT;
+    const double e = __builtin_fma(-q, T, l), c = __builtin_fma(e, rT, q);
+    return __builtin_isfinite(lf) ? c : q;
+}
+
+__host__ __device__ constexpr int sample_part_size(int V)
+{
+    return 16384 * ((V + 16384 * SAMPLE_MAX_PARTS - 1) / (16384 * SAMPLE_MAX_PARTS));
+}
+__host__ __device__ constexpr int sample_parts(int V) { return (V + sample_part_size(V) - 1) / sample_part_size(V); }
+
+// Columns [v0, v1) of one row, by 256 threads (tid 0 .. 255, four whole
+// wavefronts); red: their 4 x 3 doubles of LDS.  Every group of a workgroup
+// calls it together (it holds barriers); v0 >= v1 does nothing else.
+__device__ __forceinline__ SamplePart sample_part(const float *__restrict__ l, int v0, int v1, float tf, uint64_t seed,
+                                                  int t, int tid, double *red)
+{
+    const int lane = tid & 63, wave = tid >> 6;
     const bool greedy = !(tf > 0.0f);
-    const double T = greedy ? 1.0 : (double)tf;
-    const uint32_t k0 = (uint32_t)seed[r], k1 = (uint32_t)(seed[r] >> 32);
-    const int t = pos[r];
+    const double T = greedy ? 1.0 : (double)tf, rT = 1.0 / T;
+    const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
+    double bz = -INFINITY;
+    int bi = 0x7fffffff;
+    float lmax = -INFINITY;
+    if (greedy) {
+        float bl = -INFINITY;                         // comparing logits is comparing their doubles
+        for (int v = v0 + tid; v < v1; v += 256) {
+            const float x = l[v];
+            if (x > bl || (x == bl && v < bi)) {
+                bl = x;
+                bi = v;
+            }
+            lmax = fmaxf(lmax, x);
+        }
+        bz = (double)bl;
+    } else {
+        double b = -INFINITY;                         // the wavefront's best score
+        for (int v = v0 + tid; v < v1; v += 256) {
+            const float lf = l[v];
+            lmax = fmaxf(lmax, lf);
+            uint32_t c[4] = {(uint32_t)t, (uint32_t)v, 0u, 0u};
+            philox4x32_10(c, k0, k1);
+            const float s = (float)(0x3FFFFFFu - (c[0] >> 6)) * 0x1p-26f;   // <= 1 - u but for its own rounding
+            const float d = (float)__builtin_fma((double)lf, rT, -b);
+            if (!(s > __builtin_amdgcn_exp2f(d * 1.44269504f) * 1.001f)) {
+                better_d(bz, bi, div_by(lf, T, rT) + gumbel_noise(c[0], c[1]), v);
+            }
+            // the wavefront's new best, where some lane has one (lanes' trip
+            // counts differ by at most one, so an exchange with lanes that
+            // have left the loop is the last iteration's, after which b is
+            // not read)
+            if (__ballot(bz > b)) {
+                double m = bz;
+#pragma unroll
+                for (int off = 1; off < 64; off <<= 1) m = fmax(m, __shfl_xor(m, off, 64));
+                b = m;
+            }
+        }
+    }
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        better_d(bz, bi, __shfl_xor(bz, off, 64), __shfl_xor(bi, off, 64));
+        lmax = fmaxf(lmax, __shfl_xor(lmax, off, 64));
+    }
+    if (lane == 0) {
+        red[3 * wave] = bz;
+        red[3 * wave + 1] = (double)bi;
+        red[3 * wave + 2] = (double)lmax;
+    }
+    __syncthreads();
+    bz = red[0];
+    bi = (int)red[1];
+    lmax = (float)red[2];
+    for (int w = 1; w < 4; ++w) {
+        better_d(bz, bi, red[3 * w], (int)red[3 * w + 1]);
+        lmax = fmaxf(lmax, (float)red[3 * w + 2]);
+    }
+    const double M = div_by(lmax, T, rT);             // the largest l / T: the quotient keeps the order
+    double S = 0.0;
+    if (lmax != -INFINITY)                            // all -inf: no weight, whatever the other parts hold
+        for (int v = v0 + tid; v < v1; v += 256) S += exp(div_by(l[v], T, rT) - M);
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) S += __shfl_xor(S, off, 64);
+    __syncthreads();                                  // every thread has read red
+    if (lane == 0) red[3 * wave] = S;
+    __syncthreads();
+    return SamplePart{bz, M, ((red[0] + red[3]) + red[6]) + red[9], bi, 0};
+}
+
+// Token and log-probability of a row from its parts, by one wavefront.
+__device__ __forceinline__ void sample_merge(const SamplePart *parts, int np, const float *l, int V, float tf, int lane,
+                                             int32_t *token, float *logprob)
+{
+    const double T = tf > 0.0f ? (double)tf : 1.0;
     double bz = -INFINITY, M = -INFINITY;
     int bi = 0x7fffffff;
-    for (int v = tid; v < V; v += 1024) {
-        const double x = (double)l[v] / T;
-        const double z = greedy ? x : x + gumbel_noise(k0, k1, t, v);
-        better_d(bz, bi, z, v);
-        M = fmax(M, x);
+    for (int p = lane; p < np; p += 64) {
+        better_d(bz, bi, parts[p].z, parts[p].i);
+        M = fmax(M, parts[p].M);
     }
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
         better_d(bz, bi, __shfl_xor(bz, off, 64), __shfl_xor(bi, off, 64));
         M = fmax(M, __shfl_xor(M, off, 64));
     }
-    if (lane == 0) {
-        sz[wave] = bz;
-        si[wave] = bi;
-        sm[wave] = M;
-    }
-    __syncthreads();
-    bz = sz[0];
-    bi = si[0];
-    M = sm[0];
-    for (int w = 1; w < 16; ++w) {
-        better_d(bz, bi, sz[w], si[w]);
-        M = fmax(M, sm[w]);
-    }
     double S = 0.0;
-    for (int v = tid; v < V; v += 1024) S += exp((double)l[v] / T - M);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) S += __shfl_xor(S, off, 64);
-    __syncthreads();                                  // every thread has read sz/si/sm
-    if (lane == 0) sm[wave] = S;
-    __syncthreads();
-    if (tid == 0) {
-        double Ssum = 0.0;
-        for (int w = 0; w < 16; ++w) Ssum += sm[w];
-        token[r] = bi;
-        logprob[r] = (float)((double)l[bi] / T - M - log(Ssum));
+    for (int p0 = 0; p0 < np; p0 += 64) {             // 64 parts' terms together, added in part order
+        const int p = p0 + lane;
+        const double e = p < np ? parts[p].S * exp(parts[p].M - M) : 0.0;
+        for (int k = 0; k < 64 && p0 + k < np; ++k) S += __shfl(e, k, 64);
+    }
+    if (lane == 0) {
+        *token = bi;
+        *logprob = bi < V ? (float)((double)l[bi] / T - M - log(S)) : NAN;   // no column ever won: a row of NaN
     }
 }
 
+__global__ __launch_bounds__(256) void k_sample_part(const float *__restrict__ logits, long long ld, int V, int rows,
+                                                     const uint8_t *__restrict__ valid, const int32_t *__restrict__ pos,
+                                                     const uint64_t *__restrict__ seed, const float *__restrict__ temp,
+                                                     SamplePart *__restrict__ parts)
+{
+    __shared__ double red[12];
+    const int r = blockIdx.y, p = blockIdx.x, ps = sample_part_size(V);
+    if (!valid[r]) return;
+    const SamplePart sp = sample_part(logits + (size_t)r * ld, p * ps, min(V, (p + 1) * ps), temp[r], seed[r], pos[r],
+                                      threadIdx.x, red);
+    if (threadIdx.x == 0) parts[(size_t)r * gridDim.x + p] = sp;
+}
+
+__global__ __launch_bounds__(64) void k_sample_merge(const float *__restrict__ logits, long long ld, int V, int np,
+                                                     const uint8_t *__restrict__ valid, const float *__restrict__ temp,
+                                                     const SamplePart *__restrict__ parts, int32_t *__restrict__ token,
+                                                     float *__restrict__ logprob)
+{
+    const int r = blockIdx.x, lane = threadIdx.x;
+    if (!valid[r]) {
+        if (lane == 0) {
+            token[r] = -1;
+            logprob[r] = 0.f;
+        }
+        return;
+    }
+    sample_merge(parts + (size_t)r * np, np, logits + (size_t)r * ld, V, temp[r], lane, token + r, logprob + r);
+}
+
+// The same, one workgroup per row with the parts in LDS, four at a time: no
+// device scratch (corun_sample_noalloc).
+__global__ __launch_bounds__(1024) void k_sample_row(const float *__restrict__ logits, long long ld, int V,
+                                                     const uint8_t *__restrict__ valid, const int32_t *__restrict__ pos,
+                                                     const uint64_t *__restrict__ seed, const float *__restrict__ temp,
+                                                     int32_t *__restrict__ token, float *__restrict__ logprob)
+{
+    __shared__ SamplePart parts[SAMPLE_MAX_PARTS];
+    __shared__ double red[48];
+    const int r = blockIdx.x, grp = threadIdx.x >> 8, tid = threadIdx.x & 255;
+    if (!valid[r]) {
+        if (threadIdx.x == 0) {
+            token[r] = -1;
+            logprob[r] = 0.f;
+        }
+        return;
+    }
+    const int ps = sample_part_size(V), np = sample_parts(V);
+    const float *l = logits + (size_t)r * ld;
+    for (int p0 = 0; p0 < np; p0 += 4) {
+        const int p = p0 + grp, v0 = p < np ? p * ps : V;
+        const SamplePart sp = sample_part(l, v0, p < np ? min(V, v0 + ps) : V, temp[r], seed[r], pos[r], tid,
+                                          red + 12 * grp);
+        if (tid == 0 && p < np) parts[p] = sp;
+        __syncthreads();
+    }
+    if (threadIdx.x < 64)
+        sample_merge(parts, np, l, V, temp[r], threadIdx.x, token + r, logprob + r);
+}
+
+size_t sample_scratch_parts(int rows, int V) { return (size_t)rows * sample_parts(V); }
+
 hipError_t launch_sample(const float *logits, long long ld, int rows, int V, const uint8_t *valid, const int32_t *pos,
-                         const uint64_t *seed, const float *temp, int32_t *token, float *logprob, hipStream_t st)
+                         const uint64_t *seed, const float *temp, int32_t *token, float *logprob, SamplePart *scratch,
+                         hipStream_t st)
 {
     if (rows <= 0 || V <= 0) return hipErrorInvalidValue;
-    KLAUNCH(k_sample, dim3(rows), dim3(1024), 0, st, logits, ld, V, valid, pos, seed, temp, token,
-                       logprob);
+    const int np = sample_parts(V);
+    if (scratch == nullptr) {
+        KLAUNCH(k_sample_row, dim3(rows), dim3(1024), 0, st, logits, ld, V, valid, pos, seed, temp, token, logprob);
+        return hipGetLastError();
+    }
+    KLAUNCH(k_sample_part, dim3(np, rows), dim3(256), 0, st, logits, ld, V, rows, valid, pos, seed, temp, scratch);
+    KLAUNCH(k_sample_merge, dim3(rows), dim3(64), 0, st, logits, ld, V, np, valid, temp, scratch, token, logprob);
     return hipGetLastError();
 }
 

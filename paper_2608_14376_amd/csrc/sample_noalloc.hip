@@ -125,7 +125,8 @@ extern "C" corun_status corun_sample_noalloc(const float *logits_dev, int64_t ld
     NA_HIP(hipMemcpyAsync(d_pos, positions, sizeof(int32_t) * rows, hipMemcpyHostToDevice, hs));
     NA_HIP(hipMemcpyAsync(d_temp, temperature, sizeof(float) * rows, hipMemcpyHostToDevice, hs));
     NA_HIP(hipMemcpyAsync(d_valid, valid, rows, hipMemcpyHostToDevice, hs));
-    NA_HIP(corun::launch_sample(logits_dev, ld, rows, vocab, d_valid, d_pos, d_seed, d_temp, d_tok, d_lp, hs));
+    NA_HIP(corun::launch_sample(logits_dev, ld, rows, vocab, d_valid, d_pos, d_seed, d_temp, d_tok, d_lp, nullptr,
+                                hs));
     NA_HIP(hipMemcpyAsync(tokens_out, d_tok, sizeof(int32_t) * rows, hipMemcpyDeviceToHost, hs));
     if (logprobs_out) NA_HIP(hipMemcpyAsync(logprobs_out, d_lp, sizeof(float) * rows, hipMemcpyDeviceToHost, hs));
     NA_HIP(hipStreamSynchronize(hs));

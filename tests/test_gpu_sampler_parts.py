@@ -1,0 +1,50 @@
+"""The sampler's row parts (16384 columns each) and the test that spares most
+columns their fp64 logarithms: vocabularies at the parts' edges, masked
+(-inf) columns and parts, ties, flat rows, huge and tiny temperatures and
+logits, against the oracle; the scratch-free form gives the same bits."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2608_14376_amd import corun
+from paper_2608_14376_amd import workload as wl
+from tests.gpu_helpers import DEV, to_device
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("vocab", [16, 16368, 16384, 16400, 32768, 49168])
+def test_parts_match_the_oracle(vocab):
+    cfg = wl.config("tiny", n_layers=1, vocab=vocab)
+    Wg = to_device(wl.make_weights(cfg, seed=95))
+    rows = 14
+    K, V = wl.make_kv_contiguous(cfg, rows, 16, seed=96, device=DEV)
+    eng = corun.Engine(cfg, Wg, rows, K, V)
+    rng = np.random.default_rng(vocab)
+    l = rng.normal(0, 2.5, (rows, vocab)).astype(np.float32)
+    ninf = np.float32(-np.inf)
+    l[1] = 0.25                                       # flat: every column can win
+    l[2, : vocab - 1] = ninf                          # only the last column is left
+    l[3, vocab // 3:] = ninf                          # later parts masked whole
+    l[4, : 2 * vocab // 3] = ninf                     # earlier ones
+    l[5] = np.round(l[5])                             # ties
+    l[6] *= 1e5
+    l[7] *= 1e-6
+    l[8] = np.finfo(np.float32).min                   # a mask of the type's lowest value
+    l[8, vocab // 2] = 1.0
+    l[9] = np.sort(l[9])                              # every column beats the ones before it
+    T = np.array([0.6, 1.0, 0.7, 0.6, 1.3, 0.8, 1.0, 1.0, 0.6, 1.0, 1e-6, 1e4, 0.0, -1.0], np.float32)
+    valid = np.ones(rows, np.uint8)
+    pos = rng.integers(0, 1 << 20, rows).astype(np.int32)
+    seeds = rng.integers(0, 1 << 63, rows, dtype=np.uint64)
+    x = torch.from_numpy(l).to(DEV)
+    tok, lp = eng.sample(x, valid, pos, seeds, T)
+    for r in range(rows):
+        ot, olp = oracle.sample(l[r], int(seeds[r]), int(pos[r]), float(T[r]))
+        assert tok[r] == ot, (r, tok[r], ot)
+        # fp32 result of fp64 sums
+        assert abs(float(lp[r]) - olp) <= 1e-6 * max(1.0, abs(olp)), (r, lp[r], olp)
+    tok2, lp2 = corun.sample_noalloc(x, valid, pos, seeds, T)
+    assert np.array_equal(tok, tok2) and np.array_equal(lp.view(np.int32), lp2.view(np.int32))
+    eng.close()
