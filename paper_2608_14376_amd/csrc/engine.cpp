@@ -387,8 +387,14 @@ struct corun_engine {
     // decode workspace (one allocation)
     char *ws = nullptr;
     size_t ws_bytes = 0;
-    int32_t *d_tokens = nullptr, *d_seq = nullptr, *d_next = nullptr, *d_hist = nullptr, *d_counter = nullptr;
-    int32_t *d_order = nullptr, *h_order = nullptr;   // attention's row dispatch order
+    int32_t *d_next = nullptr, *d_hist = nullptr;
+    // A step's inputs: one device block and its pinned host mirror (StepInputs
+    // gives the offsets), uploaded together: tokens, positions, attention's
+    // row dispatch order, the address the logits go to, the history counter,
+    // the valid mask.
+    uint32_t *d_in = nullptr, *h_in = nullptr;
+    int32_t *d_tokens = nullptr, *d_seq = nullptr, *d_counter = nullptr, *d_order = nullptr;
+    float **d_logits_at = nullptr;
     uint8_t *d_valid = nullptr;
     float *gss = nullptr;   // plan.gv: sums of squares of 16-column groups of x, [B][hidden / 16]
     float *x = nullptr, *p_qkv = nullptr, *p_o = nullptr, *p_gu = nullptr, *p_down = nullptr, *attn_ws = nullptr,
@@ -400,12 +406,12 @@ struct corun_engine {
 
     // pinned host staging
     int32_t *h_tok = nullptr, *h_seq = nullptr, *h_next = nullptr, *h_counter = nullptr, *h_hist = nullptr;
+    int32_t *h_order = nullptr;
+    float **h_logits_at = nullptr;
     uint8_t *h_valid = nullptr;
-    // seeded sampling: device inputs/outputs [B] and one pinned host block
-    uint8_t *d_svalid = nullptr;
-    int32_t *d_spos = nullptr, *d_stok = nullptr;
-    uint64_t *d_sseed = nullptr;
-    float *d_stemp = nullptr, *d_slp = nullptr;
+    // seeded sampling: the inputs' device block and its pinned host mirror,
+    // which also holds the outputs
+    uint32_t *d_samp = nullptr;
     SamplePart *d_sparts = nullptr;
     char *h_samp = nullptr;
 
@@ -423,6 +429,18 @@ struct corun_engine {
     ArgBest *pf_amax = nullptr;
     size_t pf_part_elems = 0;
 };
+
+namespace {
+// Offsets in 32-bit words of a step's inputs for B rows.
+struct StepInputs {
+    int seq, order, logits_at, counter, valid, words;
+    explicit StepInputs(int B)
+        : seq(B), order(2 * B), logits_at((3 * B + 1) / 2 * 2), counter(logits_at + 2), valid(counter + 2),
+          words(valid + (B + 3) / 4)
+    {
+    }
+};
+}  // namespace
 
 // ---------------------------------------------------------------------------
 // Host-side checks
@@ -598,7 +616,7 @@ bool takes_packed(const Proj &p) { return p.bn == 128 && (p.bm == 32 || p.bm == 
 // tile-packed copy where it holds one and the plan's kernel takes it (the
 // results are bit-identical), else from the caller's row-major weight.
 hipError_t proj(corun_engine *e, const uint16_t *A, int lda, int w, int l, const Proj &pr, int rows, float *out,
-                long long split_stride, int ldo, ArgBest *amax = nullptr)
+                long long split_stride, int ldo, HeadOut head = HeadOut{})
 {
     GemmShape g = shape_of(pr, rows);
     const uint16_t *W = row_major_weight(e, w, l);
@@ -607,7 +625,7 @@ hipError_t proj(corun_engine *e, const uint16_t *A, int lda, int w, int l, const
         g.pk = 1;
         W = pk[w == W_LM_HEAD ? 0 : l];
     }
-    return launch_proj(A, lda, W, g, out, split_stride, ldo, e->st, amax);
+    return launch_proj(A, lda, W, g, out, split_stride, ldo, e->st, head);
 }
 
 // Whether gate/up and SwiGLU run as one kernel for this plan: the engine
@@ -629,7 +647,7 @@ hipError_t gate_up_swiglu(corun_engine *e, const uint16_t *A, int l, const Proj 
     GemmShape g = shape_of(pr, rows);
     if (gu_fuses_wide(pr)) return launch_gate_up_wide(A, e->c.hidden, e->w_gu[l], g, act, e->c.ffn, e->st);
     g.pk = 1;
-    return launch_gemm_dma(A, e->c.hidden, e->packed[W_GATE_UP][l], g, nullptr, 0, e->c.ffn, e->st, nullptr, act);
+    return launch_gemm_dma(A, e->c.hidden, e->packed[W_GATE_UP][l], g, nullptr, 0, e->c.ffn, e->st, HeadOut{}, act);
 }
 
 // Buffers of one mixture-of-experts layer run over `rows` rows.
@@ -870,7 +888,7 @@ corun_status launch_one(corun_engine *e, int which, int l)
         break;
     case CORUN_K_LM_HEAD:
         if (p.lm.S == 1) {
-            HIP_TRY(proj(e, e->h, H, W_LM_HEAD, 0, p.lm, B, e->logits, 0, c.vocab, e->amax));
+            HIP_TRY(proj(e, e->h, H, W_LM_HEAD, 0, p.lm, B, nullptr, 0, c.vocab, HeadOut{e->amax, e->d_logits_at}));
         } else {   // test aid only: a split lm_head, reduced in split order
             HIP_TRY(proj(e, e->h, H, W_LM_HEAD, 0, p.lm, B, e->p_lm, (long long)B * c.vocab, c.vocab));
             HIP_TRY(launch_reduce_splits(e->p_lm, p.lm.S, (long long)B * c.vocab, (long long)B * c.vocab, e->logits,
@@ -879,7 +897,7 @@ corun_status launch_one(corun_engine *e, int which, int l)
         break;
     case CORUN_K_ARGMAX:
         if (p.lm.S == 1)
-            HIP_TRY(launch_argmax_partials(e->amax, B, gemm_col_blocks(c.vocab), e->d_valid, e->d_next, st));
+            HIP_TRY(launch_argmax_partials(e->amax, B, gemm_col_blocks(c.vocab), e->d_valid, e->d_next, e->h_next, st));
         else
             HIP_TRY(launch_argmax(e->logits, B, c.vocab, e->d_valid, e->d_next, st));
         break;
@@ -1307,13 +1325,10 @@ extern "C" corun_status corun_engine_create(const corun_model_cfg *cfg, const co
     const int rope_len = std::max(cap, o.max_prefill_len);
     e->hist_cap = 4096;
     Carver cv;
-    cv.take(&e->d_tokens, B);
-    cv.take(&e->d_seq, B);
+    const StepInputs in(B);
+    cv.take(&e->d_in, in.words);
     cv.take(&e->d_next, B);
-    cv.take(&e->d_counter, 4);
     cv.take(&e->d_hist, (size_t)e->hist_cap * B);
-    cv.take(&e->d_valid, B);
-    cv.take(&e->d_order, B);
     cv.take(&e->x, (size_t)B * H);
     cv.take(&e->gss, p.gv ? (size_t)B * (H / 16) : 1);
     cv.take(&e->p_qkv, proj_part_elems(p.qkv, B));
@@ -1339,12 +1354,7 @@ extern "C" corun_status corun_engine_create(const corun_model_cfg *cfg, const co
             cv.take(&e->rt_logit, (size_t)L * B * cfg->n_experts);
         }
     }
-    cv.take(&e->d_svalid, (size_t)B);
-    cv.take(&e->d_spos, (size_t)B);
-    cv.take(&e->d_stok, (size_t)B);
-    cv.take(&e->d_sseed, (size_t)B);
-    cv.take(&e->d_stemp, (size_t)B);
-    cv.take(&e->d_slp, (size_t)B);
+    cv.take(&e->d_samp, (size_t)4 * B + (B + 3) / 4);
     cv.take(&e->d_sparts, sample_scratch_parts(B, cfg->vocab));
     cv.take(&e->h, (size_t)p.Mp * H);
     cv.take(&e->q, (size_t)B * nq * d);
@@ -1353,15 +1363,20 @@ extern "C" corun_status corun_engine_create(const corun_model_cfg *cfg, const co
     size_t total = cv.take(&e->rope, (size_t)rope_len * (d / 2));
     e->ws_bytes = total;
     if (hipMalloc(&e->ws, total) != hipSuccess) return bail(fail(CORUN_E_HIP, "workspace allocation of %zu bytes", total));
-    rebase(e->d_tokens, e->ws); rebase(e->d_seq, e->ws); rebase(e->d_next, e->ws); rebase(e->d_counter, e->ws);
-    rebase(e->d_hist, e->ws); rebase(e->d_valid, e->ws); rebase(e->d_order, e->ws); rebase(e->x, e->ws);
+    rebase(e->d_in, e->ws);
+    e->d_tokens = reinterpret_cast<int32_t *>(e->d_in);
+    e->d_seq = e->d_tokens + in.seq;
+    e->d_order = e->d_tokens + in.order;
+    e->d_logits_at = reinterpret_cast<float **>(e->d_in + in.logits_at);
+    e->d_counter = e->d_tokens + in.counter;
+    e->d_valid = reinterpret_cast<uint8_t *>(e->d_in + in.valid);
+    rebase(e->d_next, e->ws); rebase(e->d_hist, e->ws); rebase(e->x, e->ws);
     rebase(e->gss, e->ws);
     rebase(e->p_qkv, e->ws);
     rebase(e->p_o, e->ws); rebase(e->p_gu, e->ws); rebase(e->p_down, e->ws); rebase(e->attn_ws, e->ws);
     rebase(e->logits, e->ws); rebase(e->p_lm, e->ws); rebase(e->amax, e->ws); rebase(e->h, e->ws); rebase(e->q, e->ws); rebase(e->o, e->ws); rebase(e->a, e->ws);
     rebase(e->rope, e->ws);
-    rebase(e->d_svalid, e->ws); rebase(e->d_spos, e->ws); rebase(e->d_stok, e->ws); rebase(e->d_sseed, e->ws);
-    rebase(e->d_stemp, e->ws); rebase(e->d_slp, e->ws); rebase(e->d_sparts, e->ws);
+    rebase(e->d_samp, e->ws); rebase(e->d_sparts, e->ws);
     if (moe) {
         rebase(e->p_router, e->ws); rebase(e->moe_w, e->ws); rebase(e->moe_gu, e->ws); rebase(e->moe_y, e->ws);
         rebase(e->moe_sel, e->ws); rebase(e->moe_list, e->ws); rebase(e->moe_tiles, e->ws); rebase(e->moe_act, e->ws);
@@ -1380,15 +1395,17 @@ extern "C" corun_status corun_engine_create(const corun_model_cfg *cfg, const co
         launch_iota(e->d_order, B, e->st) != hipSuccess)   // a valid row order before the first upload
         return bail(fail(CORUN_E_HIP, "workspace initialisation failed"));
 
-    if (hipHostMalloc((void **)&e->h_tok, sizeof(int32_t) * B * 5 + 64, 0) != hipSuccess ||
-        hipHostMalloc((void **)&e->h_valid, B + 64, 0) != hipSuccess ||
+    if (hipHostMalloc((void **)&e->h_in, sizeof(uint32_t) * in.words, 0) != hipSuccess ||
+        hipHostMalloc((void **)&e->h_next, sizeof(int32_t) * std::max(B, CORUN_MAX_PREFILL_BATCH), 0) != hipSuccess ||
         hipHostMalloc((void **)&e->h_hist, sizeof(int32_t) * (size_t)e->hist_cap * B, 0) != hipSuccess ||
         hipHostMalloc((void **)&e->h_samp, (size_t)B * 32 + 256, 0) != hipSuccess)
         return bail(fail(CORUN_E_HIP, "pinned staging allocation failed"));
-    e->h_seq = e->h_tok + B;
-    e->h_next = e->h_tok + 2 * B;
-    e->h_counter = e->h_tok + 3 * B;
-    e->h_order = e->h_tok + 4 * B;
+    e->h_tok = reinterpret_cast<int32_t *>(e->h_in);
+    e->h_seq = e->h_tok + in.seq;
+    e->h_order = e->h_tok + in.order;
+    e->h_logits_at = reinterpret_cast<float **>(e->h_in + in.logits_at);
+    e->h_counter = e->h_tok + in.counter;
+    e->h_valid = reinterpret_cast<uint8_t *>(e->h_in + in.valid);
 
     if (o.max_prefill_len > 0) {
         e->pf_max = o.max_prefill_len;
@@ -1413,8 +1430,8 @@ extern "C" void corun_engine_destroy(corun_engine *e)
     if (e->ws) (void)hipFree(e->ws);
     if (e->pws) (void)hipFree(e->pws);
     if (e->pk_buf) (void)hipFree(e->pk_buf);
-    if (e->h_tok) (void)hipHostFree(e->h_tok);
-    if (e->h_valid) (void)hipHostFree(e->h_valid);
+    if (e->h_in) (void)hipHostFree(e->h_in);
+    if (e->h_next) (void)hipHostFree(e->h_next);
     if (e->h_hist) (void)hipHostFree(e->h_hist);
     if (e->h_samp) (void)hipHostFree(e->h_samp);
     for (hipEvent_t ev : e->rec.pool) (void)hipEventDestroy(ev);
@@ -1427,8 +1444,10 @@ extern "C" void corun_engine_destroy(corun_engine *e)
 // Decode
 // ---------------------------------------------------------------------------
 
+// The step's inputs to the device, `logits` the address its logits go to
+// (nullptr: the engine's own buffer).
 static corun_status upload_inputs(corun_engine *e, const int32_t *tokens, const uint8_t *valid,
-                                  const int32_t *seq_lens, int32_t counter)
+                                  const int32_t *seq_lens, int32_t counter, float *logits)
 {
     const int B = e->B;
     std::memcpy(e->h_tok, tokens, sizeof(int32_t) * B);
@@ -1443,11 +1462,8 @@ static corun_status upload_inputs(corun_engine *e, const int32_t *tokens, const 
         if (va != vb) return va;
         return va && seq_lens[a] > seq_lens[b];
     });
-    HIP_TRY(hipMemcpyAsync(e->d_order, e->h_order, sizeof(int32_t) * B, hipMemcpyHostToDevice, e->st));
-    HIP_TRY(hipMemcpyAsync(e->d_tokens, e->h_tok, sizeof(int32_t) * B, hipMemcpyHostToDevice, e->st));
-    HIP_TRY(hipMemcpyAsync(e->d_seq, e->h_seq, sizeof(int32_t) * B, hipMemcpyHostToDevice, e->st));
-    HIP_TRY(hipMemcpyAsync(e->d_valid, e->h_valid, B, hipMemcpyHostToDevice, e->st));
-    HIP_TRY(hipMemcpyAsync(e->d_counter, e->h_counter, sizeof(int32_t), hipMemcpyHostToDevice, e->st));
+    *e->h_logits_at = logits ? logits : e->logits;
+    HIP_TRY(launch_copy_u32(e->d_in, e->h_in, StepInputs(B).words, e->st));
     e->decoded = true;
     return CORUN_OK;
 }
@@ -1457,11 +1473,9 @@ static corun_status upload_inputs(corun_engine *e, const int32_t *tokens, const 
 // the capacity, and a kernel launched on that state would write past it.
 static corun_status restore_inputs(corun_engine *e)
 {
-    const int B = e->B;
-    HIP_TRY(hipMemcpyAsync(e->d_order, e->h_order, sizeof(int32_t) * B, hipMemcpyHostToDevice, e->st));
-    HIP_TRY(hipMemcpyAsync(e->d_tokens, e->h_tok, sizeof(int32_t) * B, hipMemcpyHostToDevice, e->st));
-    HIP_TRY(hipMemcpyAsync(e->d_seq, e->h_seq, sizeof(int32_t) * B, hipMemcpyHostToDevice, e->st));
-    HIP_TRY(hipMemcpyAsync(e->d_valid, e->h_valid, B, hipMemcpyHostToDevice, e->st));
+    *e->h_counter = e->hist_cap;          // no history
+    *e->h_logits_at = e->logits;          // not a caller's buffer of an earlier call
+    HIP_TRY(launch_copy_u32(e->d_in, e->h_in, StepInputs(e->B).words, e->st));
     return CORUN_OK;
 }
 
@@ -1471,11 +1485,14 @@ extern "C" corun_status corun_decode_step(corun_engine *e, const int32_t *tokens
     if (!e || !next_tokens) return fail(CORUN_E_INVAL, "null argument");
     ST_TRY(check_pages(e, seq_lens, valid, tokens, e->B, 1));
     ST_TRY(enter(e));
-    ST_TRY(upload_inputs(e, tokens, valid, seq_lens, e->hist_cap));
+    // an unsplit lm_head (every plan but the split-K test aid's) writes the
+    // caller's logits, and its argmax the host's tokens
+    const bool split_lm = e->plan.lm.S > 1;
+    ST_TRY(upload_inputs(e, tokens, valid, seq_lens, e->hist_cap, split_lm ? nullptr : logits));
     ST_TRY(run_step(e));
     const int B = e->B;
-    HIP_TRY(hipMemcpyAsync(e->h_next, e->d_next, sizeof(int32_t) * B, hipMemcpyDeviceToHost, e->st));
-    if (logits)
+    if (split_lm) HIP_TRY(hipMemcpyAsync(e->h_next, e->d_next, sizeof(int32_t) * B, hipMemcpyDeviceToHost, e->st));
+    if (split_lm && logits)
         HIP_TRY(hipMemcpyAsync(logits, e->logits, sizeof(float) * (size_t)B * e->c.vocab, hipMemcpyDeviceToDevice,
                                e->st));
     HIP_TRY(hipStreamSynchronize(e->st));
@@ -1496,11 +1513,11 @@ extern "C" corun_status corun_decode_run(corun_engine *e, int32_t n_steps, const
     while (done < n_steps) {
         const int n = std::min(n_steps - done, e->hist_cap);
         if (first) {
-            ST_TRY(upload_inputs(e, tokens, valid, seq_lens, 0));
+            ST_TRY(upload_inputs(e, tokens, valid, seq_lens, 0, nullptr));
             first = false;
         } else {
             *e->h_counter = 0;
-            HIP_TRY(hipMemcpyAsync(e->d_counter, e->h_counter, sizeof(int32_t), hipMemcpyHostToDevice, e->st));
+            HIP_TRY(launch_copy_u32((uint32_t *)e->d_counter, (const uint32_t *)e->h_counter, 1, e->st));
         }
         for (int i = 0; i < n; ++i) ST_TRY(run_step(e));
         HIP_TRY(hipMemcpyAsync(e->h_hist, e->d_hist, sizeof(int32_t) * (size_t)n * B, hipMemcpyDeviceToHost, e->st));
@@ -1601,11 +1618,9 @@ extern "C" corun_status corun_prefill_chunk(corun_engine *e, const int32_t *toke
     }
     HIP_TRY(launch_rmsnorm(e->pf_x + last, e->pf_part + last, dense_S, (long long)Lp * H, 1, H, e->final_norm,
                            c.rms_eps, e->pf_hlast, st, lf));
-    HIP_TRY(proj(e, e->pf_hlast, H, W_LM_HEAD, 0, pl, 1, e->pf_logits, 0, c.vocab, e->pf_amax));
-    HIP_TRY(launch_argmax_partials(e->pf_amax, 1, gemm_col_blocks(c.vocab), nullptr, e->pf_next, st));
-    HIP_TRY(hipMemcpyAsync(e->h_next, e->pf_next, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    if (last_logits)
-        HIP_TRY(hipMemcpyAsync(last_logits, e->pf_logits, sizeof(float) * c.vocab, hipMemcpyDeviceToDevice, st));
+    HIP_TRY(proj(e, e->pf_hlast, H, W_LM_HEAD, 0, pl, 1, last_logits ? last_logits : e->pf_logits, 0, c.vocab,
+                 HeadOut{e->pf_amax}));
+    HIP_TRY(launch_argmax_partials(e->pf_amax, 1, gemm_col_blocks(c.vocab), nullptr, e->pf_next, e->h_next, st));
     HIP_TRY(hipStreamSynchronize(st));
     if (token_out) *token_out = e->h_next[0];
     return CORUN_OK;
@@ -1721,13 +1736,11 @@ extern "C" corun_status corun_prefill_batch(corun_engine *e, const int32_t *toke
     HIP_TRY(launch_rmsnorm(e->pf_x, e->pf_part, dense_S, (long long)Lp * H, Lp, H, e->final_norm, c.rms_eps, e->pf_h,
                            st, fold_of(e, pmb, c.n_layers)));
     HIP_TRY(launch_gather_last_rows(e->pf_h, e->pf_seq, n, H, e->pf_hlast, st));
-    HIP_TRY(proj(e, e->pf_hlast, H, W_LM_HEAD, 0, pl, n, e->pf_logits, 0, c.vocab, e->pf_amax));
-    HIP_TRY(launch_argmax_partials(e->pf_amax, n, gemm_col_blocks(c.vocab), nullptr, e->pf_next, st));
-    HIP_TRY(hipMemcpyAsync(tokens_out, e->pf_next, sizeof(int32_t) * n, hipMemcpyDeviceToHost, st));
-    if (last_logits)
-        HIP_TRY(hipMemcpyAsync(last_logits, e->pf_logits, sizeof(float) * (size_t)n * c.vocab,
-                               hipMemcpyDeviceToDevice, st));
+    HIP_TRY(proj(e, e->pf_hlast, H, W_LM_HEAD, 0, pl, n, last_logits ? last_logits : e->pf_logits, 0, c.vocab,
+                 HeadOut{e->pf_amax}));
+    HIP_TRY(launch_argmax_partials(e->pf_amax, n, gemm_col_blocks(c.vocab), nullptr, e->pf_next, e->h_next, st));
     HIP_TRY(hipStreamSynchronize(st));
+    std::memcpy(tokens_out, e->h_next, sizeof(int32_t) * n);
     return CORUN_OK;
 }
 
@@ -1788,27 +1801,24 @@ extern "C" corun_status corun_sample(corun_engine *e, const float *logits_dev, i
             return fail(CORUN_E_INVAL, "row %d: temperature is not finite", r);
     }
     ST_TRY(enter(e));
-    // pinned staging: seeds [B] u64, positions [B], temperatures [B], tokens [B], logprobs [B], valid [B]
+    // pinned staging: seeds u64, positions, temperatures, valid flags [rows],
+    // uploaded together; past that block's largest size the outputs, which the
+    // kernel writes itself
     char *hs = e->h_samp;
-    uint64_t *hseed = reinterpret_cast<uint64_t *>(hs);
-    int32_t *hpos = reinterpret_cast<int32_t *>(hs + 8 * (size_t)e->B);
-    float *htemp = reinterpret_cast<float *>(hs + 12 * (size_t)e->B);
-    int32_t *htok = reinterpret_cast<int32_t *>(hs + 16 * (size_t)e->B);
-    float *hlp = reinterpret_cast<float *>(hs + 20 * (size_t)e->B);
-    uint8_t *hval = reinterpret_cast<uint8_t *>(hs + 24 * (size_t)e->B);
-    std::memcpy(hseed, seeds, sizeof(uint64_t) * rows);
-    std::memcpy(hpos, positions, sizeof(int32_t) * rows);
-    std::memcpy(htemp, temperature, sizeof(float) * rows);
-    std::memcpy(hval, valid, rows);
+    const size_t B = (size_t)e->B, R = (size_t)rows;
+    const int words = 4 * rows + (rows + 3) / 4;
+    int32_t *htok = reinterpret_cast<int32_t *>(hs + 4 * (4 * B + (B + 3) / 4));
+    float *hlp = reinterpret_cast<float *>(htok + B);
+    std::memcpy(hs, seeds, sizeof(uint64_t) * R);
+    std::memcpy(hs + 8 * R, positions, sizeof(int32_t) * R);
+    std::memcpy(hs + 12 * R, temperature, sizeof(float) * R);
+    std::memcpy(hs + 16 * R, valid, R);
     hipStream_t st = e->st;
-    HIP_TRY(hipMemcpyAsync(e->d_sseed, hseed, sizeof(uint64_t) * rows, hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(e->d_spos, hpos, sizeof(int32_t) * rows, hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(e->d_stemp, htemp, sizeof(float) * rows, hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(e->d_svalid, hval, rows, hipMemcpyHostToDevice, st));
-    HIP_TRY(launch_sample(logits_dev, ld, rows, e->c.vocab, e->d_svalid, e->d_spos, e->d_sseed, e->d_stemp,
-                          e->d_stok, e->d_slp, e->d_sparts, st));
-    HIP_TRY(hipMemcpyAsync(htok, e->d_stok, sizeof(int32_t) * rows, hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipMemcpyAsync(hlp, e->d_slp, sizeof(float) * rows, hipMemcpyDeviceToHost, st));
+    const char *ds = reinterpret_cast<const char *>(e->d_samp);
+    HIP_TRY(launch_copy_u32(e->d_samp, reinterpret_cast<const uint32_t *>(hs), words, st));
+    HIP_TRY(launch_sample(logits_dev, ld, rows, e->c.vocab, reinterpret_cast<const uint8_t *>(ds + 16 * R),
+                          reinterpret_cast<const int32_t *>(ds + 8 * R), reinterpret_cast<const uint64_t *>(ds),
+                          reinterpret_cast<const float *>(ds + 12 * R), htok, hlp, e->d_sparts, st));
     HIP_TRY(hipStreamSynchronize(st));
     std::memcpy(tokens_out, htok, sizeof(int32_t) * rows);
     if (logprobs_out) std::memcpy(logprobs_out, hlp, sizeof(float) * rows);

@@ -85,6 +85,14 @@ struct ArgBest {
     int i;
 };
 
+// lm_head: its epilogue's argmax partials (S == 1 only; per row m and column
+// block cb of 64 columns, amax[m * ceil(N / 64) + cb]), and optionally where in
+// device memory the address of the outputs stands (then `out` is not used).
+struct HeadOut {
+    ArgBest *amax = nullptr;
+    float *const *out_at = nullptr;
+};
+
 // The QKV projection's split partials for an attention kernel that applies
 // the QKV epilogue itself (launch_attn_split): part [S][rows][(nq + 2 nkv) d]
 // with split stride `stride`, and the RoPE table.
@@ -116,15 +124,13 @@ struct GemmShape {
 };
 // Dispatch on g.bm.
 hipError_t launch_proj(const uint16_t *A, int lda, const uint16_t *W, const GemmShape &g, float *out,
-                       long long split_stride, int ldo, hipStream_t st, ArgBest *amax = nullptr);
-// With amax != nullptr (S == 1 only) the epilogue also writes, per row m and
-// column block cb of 64 columns, amax[m * ceil(N / 64) + cb].
+                       long long split_stride, int ldo, hipStream_t st, HeadOut head = HeadOut{});
 hipError_t launch_gemm(const uint16_t *A, int lda, const uint16_t *W, const GemmShape &g, float *out,
-                       long long split_stride, int ldo, hipStream_t st, ArgBest *amax = nullptr);
+                       long long split_stride, int ldo, hipStream_t st, HeadOut head = HeadOut{});
 // LDS-tiled variant for large M: tiles of bm (64, 128 or 256) x 128, split-K
 // over grid.y, same output contract as launch_gemm (no argmax epilogue).
 hipError_t launch_gemm_tiled(const uint16_t *A, int lda, const uint16_t *W, const GemmShape &g, int bm, float *out,
-                             long long split_stride, int ldo, hipStream_t st, ArgBest *amax = nullptr);
+                             long long split_stride, int ldo, hipStream_t st, HeadOut head = HeadOut{});
 // Pipelined variant (direct global -> LDS loads, 32x32 MFMA tiles): K and Kc
 // multiples of 64; 32 x 128 and 64 x 128 tiles, and the wide ones 128 x 128,
 // 256 x 128, 256 x 256 and 320 x 256.
@@ -133,7 +139,7 @@ hipError_t launch_gemm_tiled(const uint16_t *A, int lda, const uint16_t *W, cons
 // with interleave) and the kernel writes act[m * ldo + j] = SwiGLU of
 // feature j (bf16) instead of fp32 outputs; out and amax are unused.
 hipError_t launch_gemm_dma(const uint16_t *A, int lda, const uint16_t *W, const GemmShape &g, float *out,
-                           long long split_stride, int ldo, hipStream_t st, ArgBest *amax = nullptr,
+                           long long split_stride, int ldo, hipStream_t st, HeadOut head = HeadOut{},
                            uint16_t *act = nullptr);
 // act[m][j] = SwiGLU of feature j (bf16, ld ldo) from the row-major [2F, K]
 // gate/up weight, the wide tile g.bm x g.bn, no split-K (K % 64 == 0): the
@@ -141,9 +147,12 @@ hipError_t launch_gemm_dma(const uint16_t *A, int lda, const uint16_t *W, const 
 hipError_t launch_gate_up_wide(const uint16_t *A, int lda, const uint16_t *W, const GemmShape &g, uint16_t *act, int ldo,
                                hipStream_t st);
 inline int gemm_col_blocks(int N) { return (N + 63) / 64; }
-// next[r] = best index over the np column-block partials of row r (-1 for padding rows).
+// next[r] = host[r] (pinned host memory) = best index over the np column-block
+// partials of row r (-1 for padding rows).
 hipError_t launch_argmax_partials(const ArgBest *part, int rows, int np, const uint8_t *valid, int32_t *next,
-                                  hipStream_t st);
+                                  int32_t *host, hipStream_t st);
+// n words from pinned host memory, in one workgroup.
+hipError_t launch_copy_u32(uint32_t *dst, const uint32_t *src, int n, hipStream_t st);
 
 // Reduce QKV partials, round to bf16, rotate q and k by their position,
 // round again, write q (bf16 [rows][nq*d]) and append k, v to the cache.

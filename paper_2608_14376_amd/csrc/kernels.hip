@@ -78,6 +78,14 @@ __device__ __forceinline__ uint32_t f2bf2(float a, float b)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t){a, b}, bf16x2_t));
 }
 
+// where a projection's outputs go: the address it was launched with, or the
+// one that stands in device memory now (a captured launch whose caller's
+// buffer changes from step to step)
+__device__ __forceinline__ float *head_out(const HeadOut &head, float *out)
+{
+    return head.out_at != nullptr ? *head.out_at : out;
+}
+
 // SwiGLU of one feature from its fp32 gate and up sums: both rounded to
 // bf16 (the projection's output precision), silu(g) u rounded to bf16.  The
 // SwiGLU kernel and the gate/up projection's fused epilogue share it, so the
@@ -391,7 +399,7 @@ template <int MT, int NT, int KU>
 __global__ __launch_bounds__(256) void k_gemm(const uint16_t *__restrict__ A, int lda,
                                               const uint16_t *__restrict__ W, int M, int N, int K, int Kc,
                                               float *__restrict__ out, long long split_stride, int ldo,
-                                              ArgBest *__restrict__ amax)
+                                              HeadOut head)
 {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int r = lane & 15, kg = lane >> 4;
@@ -463,7 +471,7 @@ __global__ __launch_bounds__(256) void k_gemm(const uint16_t *__restrict__ A, in
                 acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[mt], wf[nt], acc[mt][nt], 0, 0, 0);
     }
 
-    float *o = out + (size_t)s * split_stride;
+    float *o = head_out(head, out) + (size_t)s * split_stride;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -475,7 +483,7 @@ __global__ __launch_bounds__(256) void k_gemm(const uint16_t *__restrict__ A, in
                 if (row < M) o[(size_t)row * ldo + n0 + 16 * nt + r] = acc[mt][nt][i];
             }
         }
-    if (amax != nullptr) {
+    if (head.amax != nullptr) {
         // per row: best (value, column) over this wavefront's columns -- an
         // exact selection under the "larger value, then smaller index" order
 #pragma unroll
@@ -494,7 +502,7 @@ __global__ __launch_bounds__(256) void k_gemm(const uint16_t *__restrict__ A, in
                     better(bv, bi, v2, i2);
                 }
                 const int row = m0 + 16 * mt + kg * 4 + i;
-                if (r == 0 && row < M) amax[(size_t)row * ncb + cb] = ArgBest{bv, bi};
+                if (r == 0 && row < M) head.amax[(size_t)row * ncb + cb] = ArgBest{bv, bi};
             }
     }
 }
@@ -516,7 +524,7 @@ template <int BM, int BN, int WAVES_M>
 __global__ __launch_bounds__(256) void k_gemm_tiled(const uint16_t *__restrict__ A, int lda,
                                                     const uint16_t *__restrict__ W, int M, int N, int K, int Kc,
                                                     float *__restrict__ out, long long split_stride, int ldo,
-                                                    ArgBest *__restrict__ amax)
+                                                    HeadOut head)
 {
     constexpr int BK = 64, LDR = 72;
     constexpr int WAVES_N = 4 / WAVES_M;
@@ -609,7 +617,7 @@ __global__ __launch_bounds__(256) void k_gemm_tiled(const uint16_t *__restrict__
 #undef CORUN_TILED_GLOAD
 #undef CORUN_TILED_SSTORE
 
-    float *o = out + (size_t)s * split_stride;
+    float *o = head_out(head, out) + (size_t)s * split_stride;
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -623,7 +631,7 @@ __global__ __launch_bounds__(256) void k_gemm_tiled(const uint16_t *__restrict__
             }
         }
     if constexpr (WN == 64) {
-        if (amax != nullptr) {   // per row: best over this wavefront's 64 columns (one 64-column block)
+        if (head.amax != nullptr) {   // per row: best over this wavefront's 64 columns (one 64-column block)
             const int ncb = (N + 63) / 64;
 #pragma unroll
             for (int i = 0; i < FM; ++i)
@@ -643,7 +651,7 @@ __global__ __launch_bounds__(256) void k_gemm_tiled(const uint16_t *__restrict__
                         better(bv, bi, v2, i2);
                     }
                     const int row = m0 + wm0 + 16 * i + kg * 4 + q;
-                    if (r16 == 0 && row < M && n0 + wn0 < N) amax[(size_t)row * ncb + (n0 + wn0) / 64] = ArgBest{bv, bi};
+                    if (r16 == 0 && row < M && n0 + wn0 < N) head.amax[(size_t)row * ncb + (n0 + wn0) / 64] = ArgBest{bv, bi};
                 }
         }
     }
@@ -722,7 +730,7 @@ template <int BM, int BN, int BK, int NST, int WGM, int NW = 4, bool PKW = false
 __global__ __launch_bounds__(64 * NW) void k_gemm_dma(const uint16_t *__restrict__ A, int lda,
                                                   const uint16_t *__restrict__ W, int M, int N, int K, int Kc,
                                                   float *__restrict__ out, long long split_stride, int ldo,
-                                                  ArgBest *__restrict__ amax, uint16_t *__restrict__ act,
+                                                  HeadOut head, uint16_t *__restrict__ act,
                                                   ExpertTiles et)
 {
     constexpr int C = BK / 8;                         // 16-byte chunks per row
@@ -920,7 +928,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_dma(const uint16_t *__restrict
     }
 
     // lane holds, per 32x32 tile, column r32 and rows 8 (q / 4) + 4 h + q % 4
-    float *o = out + (size_t)s * split_stride;
+    float *o = head_out(head, out) + (size_t)s * split_stride;
 #pragma unroll
     for (int a = 0; a < FM; ++a)
 #pragma unroll
@@ -934,7 +942,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_dma(const uint16_t *__restrict
             }
         }
     // every configuration the launcher uses has 64-column wavefront tiles
-    if (WN == 64 && amax != nullptr) {
+    if (WN == 64 && head.amax != nullptr) {
         // per row: best (value, column) over this wavefront's 64 columns (one
         // 64-column block).  Each 32-row fragment goes through the wavefront's
         // own padded 32 x 68 float tile in the (now idle) ring; lane l scans
@@ -967,7 +975,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_dma(const uint16_t *__restrict
             const int i2 = __shfl_xor(bi, 1, 64);
             better(bv, bi, v2, i2);
             const int row = m0 + wm0 + 32 * a + rr;
-            if (hf == 0 && row < M && n0 + wn0 < N) amax[(size_t)row * ncb + (n0 + wn0) / 64] = ArgBest{bv, bi};
+            if (hf == 0 && row < M && n0 + wn0 < N) head.amax[(size_t)row * ncb + (n0 + wn0) / 64] = ArgBest{bv, bi};
         }
     }
 }
@@ -1023,7 +1031,7 @@ template <int BM, int BN, int NST, int WGM, int NW, int EPI, bool MOE = false, b
 __global__ __launch_bounds__(64 * NW) void k_gemm_wide(const uint16_t *__restrict__ A, int lda,
                                                        const uint16_t *__restrict__ W, int M, int N, int K, int Kc,
                                                        float *__restrict__ out, long long split_stride, int ldo,
-                                                       ArgBest *__restrict__ amax, uint16_t *__restrict__ act,
+                                                       HeadOut head, uint16_t *__restrict__ act,
                                                        ExpertTiles et)
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // buffer resources exist in device code only
@@ -1241,7 +1249,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_wide(const uint16_t *__restric
                 }
         return;
     } else {
-        float *o = out + (size_t)s * split_stride;
+        float *o = head_out(head, out) + (size_t)s * split_stride;
 #pragma unroll
         for (int a = 0; a < FM; ++a)
 #pragma unroll
@@ -1254,7 +1262,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_wide(const uint16_t *__restric
                     if (row < row_end) o[out_row(row) * ldo + col] = acc[a][b][q];
                 }
             }
-        if (amax != nullptr) {
+        if (head.amax != nullptr) {
             // per row: best (value, column) over this wavefront's 64 columns.
             // Each 32-row fragment goes through the wavefront's own padded
             // 32 x 68 float tile in the idle ring (after the last barrier no
@@ -1287,7 +1295,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_wide(const uint16_t *__restric
                 const int i2 = __shfl_xor(bi, 1, 64);
                 better(bv, bi, v2, i2);
                 const int row = m0 + wm0 + 32 * a + rr;
-                if (hf == 0 && row < M && n0 + wn0 < N) amax[(size_t)row * ncb + (n0 + wn0) / 64] = ArgBest{bv, bi};
+                if (hf == 0 && row < M && n0 + wn0 < N) head.amax[(size_t)row * ncb + (n0 + wn0) / 64] = ArgBest{bv, bi};
             }
         }
     }
@@ -1297,10 +1305,10 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_wide(const uint16_t *__restric
 namespace {
 template <int BM, int BN, int NST, int WGM, int NW, int EPI, bool MOE = false, bool PKW = false>
 hipError_t wide_launch(dim3 grid, hipStream_t st, const uint16_t *A, int lda, const uint16_t *W, int M, int N, int K,
-                       int Kc, float *out, long long split_stride, int ldo, ArgBest *amax, uint16_t *act,
+                       int Kc, float *out, long long split_stride, int ldo, HeadOut head, uint16_t *act,
                        ExpertTiles et)
 {
-    KLAUNCH((k_gemm_wide<BM, BN, NST, WGM, NW, EPI, MOE, PKW>), grid, dim3(64 * NW), 0, st, A, lda, W, M, N, K, Kc, out, split_stride, ldo, amax, act, et);
+    KLAUNCH((k_gemm_wide<BM, BN, NST, WGM, NW, EPI, MOE, PKW>), grid, dim3(64 * NW), 0, st, A, lda, W, M, N, K, Kc, out, split_stride, ldo, head, act, et);
     return hipGetLastError();
 }
 
@@ -1322,7 +1330,7 @@ bool wide_tile(int bm, int bn, hipError_t &e, dim3 grid, Args... args)
 }  // namespace
 
 hipError_t launch_gemm_dma(const uint16_t *A, int lda, const uint16_t *W, const GemmShape &g, float *out,
-                           long long split_stride, int ldo, hipStream_t st, ArgBest *amax, uint16_t *act)
+                           long long split_stride, int ldo, hipStream_t st, HeadOut head, uint16_t *act)
 {
     // 32 or 64 x 128 (small batches): two wavefronts side by side (32- or
     // 64-row, 64-column wavefront tiles); above, the wide tiles.  Every
@@ -1337,33 +1345,33 @@ hipError_t launch_gemm_dma(const uint16_t *A, int lda, const uint16_t *W, const 
             if (g.S != 1 || g.N % 128 != 0) return hipErrorInvalidValue;
             if (g.bm == 32 && g.bn == 128)
                 KLAUNCH((k_gemm_dma<32, 128, 64, 4, 1, 2, true, true>), grid, dim3(128), 0, st, A, lda, W,
-                                   g.M, g.N, g.K, g.Kc, nullptr, 0, ldo, nullptr, act, ExpertTiles{});
+                                   g.M, g.N, g.K, g.Kc, nullptr, 0, ldo, HeadOut{}, act, ExpertTiles{});
             else if (g.bm == 64 && g.bn == 128)
                 KLAUNCH((k_gemm_dma<64, 128, 64, 4, 1, 2, true, true>), grid, dim3(128), 0, st, A, lda, W,
-                                   g.M, g.N, g.K, g.Kc, nullptr, 0, ldo, nullptr, act, ExpertTiles{});
+                                   g.M, g.N, g.K, g.Kc, nullptr, 0, ldo, HeadOut{}, act, ExpertTiles{});
             else
                 return hipErrorInvalidValue;
             return hipGetLastError();
         }
         if (g.bm == 32 && g.bn == 128)
             KLAUNCH((k_gemm_dma<32, 128, 64, 4, 1, 2, true>), grid, dim3(128), 0, st, A, lda, W, g.M, g.N,
-                               g.K, g.Kc, out, split_stride, ldo, amax, nullptr, ExpertTiles{});
+                               g.K, g.Kc, out, split_stride, ldo, head, nullptr, ExpertTiles{});
         else if (g.bm == 64 && g.bn == 128)
             KLAUNCH((k_gemm_dma<64, 128, 64, 4, 1, 2, true>), grid, dim3(128), 0, st, A, lda, W, g.M, g.N,
-                               g.K, g.Kc, out, split_stride, ldo, amax, nullptr, ExpertTiles{});
+                               g.K, g.Kc, out, split_stride, ldo, head, nullptr, ExpertTiles{});
         else
             return hipErrorInvalidValue;
         return hipGetLastError();
     }
     if (g.bm == 32 && g.bn == 128)
         KLAUNCH((k_gemm_dma<32, 128, 64, 4, 1, 2>), grid, dim3(128), 0, st, A, lda, W, g.M, g.N, g.K, g.Kc,
-                           out, split_stride, ldo, amax, nullptr, ExpertTiles{});
+                           out, split_stride, ldo, head, nullptr, ExpertTiles{});
     else if (g.bm == 64 && g.bn == 128)
         KLAUNCH((k_gemm_dma<64, 128, 64, 4, 1, 2>), grid, dim3(128), 0, st, A, lda, W, g.M, g.N, g.K, g.Kc,
-                           out, split_stride, ldo, amax, nullptr, ExpertTiles{});
+                           out, split_stride, ldo, head, nullptr, ExpertTiles{});
     else {
         hipError_t e = hipSuccess;
-        if (wide_tile<WIDE_F32>(g.bm, g.bn, e, grid, st, A, lda, W, g.M, g.N, g.K, g.Kc, out, split_stride, ldo, amax,
+        if (wide_tile<WIDE_F32>(g.bm, g.bn, e, grid, st, A, lda, W, g.M, g.N, g.K, g.Kc, out, split_stride, ldo, head,
                                 (uint16_t *)nullptr, ExpertTiles{}))
             return e;
         return hipErrorInvalidValue;
@@ -1381,30 +1389,30 @@ hipError_t launch_gate_up_wide(const uint16_t *A, int lda, const uint16_t *W, co
     const dim3 grid(((g.M + g.bm - 1) / g.bm) * ((g.N + g.bn - 1) / g.bn), 1);
     hipError_t e = hipSuccess;
     if (wide_tile<WIDE_SWIGLU>(g.bm, g.bn, e, grid, st, A, lda, W, g.M, g.N, g.K, g.K, (float *)nullptr, 0ll, ldo,
-                               (ArgBest *)nullptr, act, ExpertTiles{}))
+                               HeadOut{}, act, ExpertTiles{}))
         return e;
     return hipErrorInvalidValue;
 }
 
 hipError_t launch_gemm_tiled(const uint16_t *A, int lda, const uint16_t *W, const GemmShape &g, int bm, float *out,
-                             long long split_stride, int ldo, hipStream_t st, ArgBest *amax)
+                             long long split_stride, int ldo, hipStream_t st, HeadOut head)
 {
-    if (amax != nullptr && bm == 64) return hipErrorInvalidValue;   // argmax epilogue needs 64-column wavefront tiles
+    if (head.amax != nullptr && bm == 64) return hipErrorInvalidValue;   // argmax epilogue needs 64-column wavefront tiles
     const int num_n = (g.N + 127) / 128;
     const int num_m = (g.M + bm - 1) / bm;
     dim3 grid(num_m * num_n, g.S);
     switch (bm) {
     case 64:
         KLAUNCH((k_gemm_tiled<64, 128, 1>), grid, dim3(256), 0, st, A, lda, W, g.M, g.N, g.K, g.Kc, out,
-                           split_stride, ldo, amax);
+                           split_stride, ldo, head);
         break;
     case 128:
         KLAUNCH((k_gemm_tiled<128, 128, 2>), grid, dim3(256), 0, st, A, lda, W, g.M, g.N, g.K, g.Kc, out,
-                           split_stride, ldo, amax);
+                           split_stride, ldo, head);
         break;
     case 256:
         KLAUNCH((k_gemm_tiled<256, 128, 2>), grid, dim3(256), 0, st, A, lda, W, g.M, g.N, g.K, g.Kc, out,
-                           split_stride, ldo, amax);
+                           split_stride, ldo, head);
         break;
     default:
         return hipErrorInvalidValue;
@@ -1413,7 +1421,7 @@ hipError_t launch_gemm_tiled(const uint16_t *A, int lda, const uint16_t *W, cons
 }
 
 hipError_t launch_gemm(const uint16_t *A, int lda, const uint16_t *W, const GemmShape &g, float *out,
-                       long long split_stride, int ldo, hipStream_t st, ArgBest *amax)
+                       long long split_stride, int ldo, hipStream_t st, HeadOut head)
 {
     constexpr int NT = 4;
     const int ncb = (g.N + 16 * NT - 1) / (16 * NT);
@@ -1422,15 +1430,15 @@ hipError_t launch_gemm(const uint16_t *A, int lda, const uint16_t *W, const Gemm
     switch (g.mt) {
     case 1:
         KLAUNCH((k_gemm<1, NT, 4>), grid, dim3(256), 0, st, A, lda, W, g.M, g.N, g.K, g.Kc, out,
-                           split_stride, ldo, amax);
+                           split_stride, ldo, head);
         break;
     case 2:
         KLAUNCH((k_gemm<2, NT, 4>), grid, dim3(256), 0, st, A, lda, W, g.M, g.N, g.K, g.Kc, out,
-                           split_stride, ldo, amax);
+                           split_stride, ldo, head);
         break;
     case 4:
         KLAUNCH((k_gemm<4, NT, 2>), grid, dim3(256), 0, st, A, lda, W, g.M, g.N, g.K, g.Kc, out,
-                           split_stride, ldo, amax);
+                           split_stride, ldo, head);
         break;
     default:
         return hipErrorInvalidValue;
@@ -2227,11 +2235,15 @@ __global__ __launch_bounds__(256) void k_argmax(const float *__restrict__ logits
 }
 
 __global__ __launch_bounds__(256) void k_argmax_partials(const ArgBest *__restrict__ part, int np,
-                                                         const uint8_t *__restrict__ valid, int32_t *__restrict__ next)
+                                                         const uint8_t *__restrict__ valid, int32_t *__restrict__ next,
+                                                         int32_t *__restrict__ host)
 {
     const int r = blockIdx.x;
     if (valid != nullptr && !valid[r]) {
-        if (threadIdx.x == 0) next[r] = -1;
+        if (threadIdx.x == 0) {
+            next[r] = -1;
+            host[r] = -1;
+        }
         return;
     }
     const ArgBest *p = part + (size_t)r * np;
@@ -2253,14 +2265,16 @@ __global__ __launch_bounds__(256) void k_argmax_partials(const ArgBest *__restri
     __syncthreads();
     if (threadIdx.x == 0) {
         for (int w = 1; w < 4; ++w) better(bv, bi, sv[w], si[w]);
-        next[r] = (bi == 0x7fffffff) ? 0 : bi;
+        const int best = (bi == 0x7fffffff) ? 0 : bi;
+        next[r] = best;
+        host[r] = best;
     }
 }
 
 hipError_t launch_argmax_partials(const ArgBest *part, int rows, int np, const uint8_t *valid, int32_t *next,
-                                  hipStream_t st)
+                                  int32_t *host, hipStream_t st)
 {
-    KLAUNCH(k_argmax_partials, dim3(rows), dim3(256), 0, st, part, np, valid, next);
+    KLAUNCH(k_argmax_partials, dim3(rows), dim3(256), 0, st, part, np, valid, next, host);
     return hipGetLastError();
 }
 
@@ -2311,6 +2325,20 @@ __global__ void k_rope_table(float2 *tab, int d, double theta)
 hipError_t launch_rope_table(float2 *tab, int max_pos, int d, double theta, hipStream_t st)
 {
     KLAUNCH(k_rope_table, dim3(max_pos), dim3(64), 0, st, tab, d, theta);
+    return hipGetLastError();
+}
+
+// Copy of n words from pinned host memory: a call's few hundred bytes of
+// inputs as one launch on the stream instead of a copy engine's request per
+// array.
+__global__ __launch_bounds__(1024) void k_copy_u32(uint32_t *__restrict__ dst, const uint32_t *__restrict__ src, int n)
+{
+    for (int i = threadIdx.x; i < n; i += 1024) dst[i] = src[i];
+}
+
+hipError_t launch_copy_u32(uint32_t *dst, const uint32_t *src, int n, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_copy_u32, dim3(1), dim3(1024), 0, st, dst, src, n);
     return hipGetLastError();
 }
 
@@ -3045,13 +3073,13 @@ hipError_t launch_moe_gemm_dma(const uint16_t *A, int lda, int row_div, const ui
             switch (tile_rows) {
             case 64:
                 return wide_launch<64, 128, 2, 1, 2, EPI, true, true>(grid, st, A, lda, W, 64, N, K, K, out, 0, ldo,
-                                                                      nullptr, act, et);
+                                                                      HeadOut{}, act, et);
             case 128:
                 return wide_launch<128, 128, 2, 2, 4, EPI, true, true>(grid, st, A, lda, W, 128, N, K, K, out, 0, ldo,
-                                                                       nullptr, act, et);
+                                                                      HeadOut{}, act, et);
             case 256:
                 return wide_launch<256, 128, 3, 2, 4, EPI, true, true>(grid, st, A, lda, W, 256, N, K, K, out, 0, ldo,
-                                                                       nullptr, act, et);
+                                                                      HeadOut{}, act, et);
             default:
                 return hipErrorInvalidValue;
             }
@@ -3061,13 +3089,13 @@ hipError_t launch_moe_gemm_dma(const uint16_t *A, int lda, int row_div, const ui
     }
     if (act != nullptr)
         KLAUNCH((k_gemm_dma<32, 128, 64, 4, 1, 2, true, true, true>), grid, dim3(128), 0, st, A, lda, W, 16,
-                           N, K, K, nullptr, 0, ldo, nullptr, act, et);
+                           N, K, K, nullptr, 0, ldo, HeadOut{}, act, et);
     else if (packed)
         KLAUNCH((k_gemm_dma<32, 128, 64, 4, 1, 2, true, false, true>), grid, dim3(128), 0, st, A, lda, W,
-                           16, N, K, K, out, 0, ldo, nullptr, nullptr, et);
+                           16, N, K, K, out, 0, ldo, HeadOut{}, nullptr, et);
     else
         KLAUNCH((k_gemm_dma<32, 128, 64, 4, 1, 2, false, false, true>), grid, dim3(128), 0, st, A, lda, W,
-                           16, N, K, K, out, 0, ldo, nullptr, nullptr, et);
+                           16, N, K, K, out, 0, ldo, HeadOut{}, nullptr, et);
     return hipGetLastError();
 }
 
@@ -3677,11 +3705,11 @@ hipError_t launch_sample(const float *logits, long long ld, int rows, int V, con
 }
 
 hipError_t launch_proj(const uint16_t *A, int lda, const uint16_t *W, const GemmShape &g, float *out,
-                       long long split_stride, int ldo, hipStream_t st, ArgBest *amax)
+                       long long split_stride, int ldo, hipStream_t st, HeadOut head)
 {
-    if (g.bn > 0) return launch_gemm_dma(A, lda, W, g, out, split_stride, ldo, st, amax);
-    if (g.bm > 0) return launch_gemm_tiled(A, lda, W, g, g.bm, out, split_stride, ldo, st, amax);
-    return launch_gemm(A, lda, W, g, out, split_stride, ldo, st, amax);
+    if (g.bn > 0) return launch_gemm_dma(A, lda, W, g, out, split_stride, ldo, st, head);
+    if (g.bm > 0) return launch_gemm_tiled(A, lda, W, g, g.bm, out, split_stride, ldo, st, head);
+    return launch_gemm(A, lda, W, g, out, split_stride, ldo, st, head);
 }
 
 }  // namespace corun
