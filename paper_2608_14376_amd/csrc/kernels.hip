@@ -208,22 +208,34 @@ __device__ __forceinline__ float wave_sum_dpp(float v)
 // ---------------------------------------------------------------------------
 // Embedding gather
 // ---------------------------------------------------------------------------
-// Grid: rows x ceil(H / 256) blocks, flattened into x (rows may exceed the
-// 65535 limit of the other grid dimensions in a long prefill).  With ss
-// (H a multiple of 256) it also writes each row's sums of squares over
-// 16-column groups, ss[b][i / 16], for the small-batch projections' norm.
-__global__ void k_embed(const uint16_t *__restrict__ E, const int32_t *__restrict__ tokens,
-                        const uint8_t *__restrict__ valid, int H, float *__restrict__ x, float *__restrict__ ss)
+// Grid: rows x ceil(H / 1024) blocks, flattened into x (rows may exceed the
+// 65535 limit of the other grid dimensions in a long prefill); a thread
+// copies four elements (one element per thread took 371 us for 32768 rows of
+// 4096, bound by the number of workgroups).  With ss (H a multiple of 256) it
+// also writes each row's sums of squares over 16-column groups, ss[b][i / 16],
+// for the small-batch projections' norm: four threads' 4-element sums.
+__global__ __launch_bounds__(256) void k_embed(const uint16_t *__restrict__ E, const int32_t *__restrict__ tokens,
+                                               const uint8_t *__restrict__ valid, int H, float *__restrict__ x,
+                                               float *__restrict__ ss)
 {
-    const int nb = (H + 255) / 256;
+    const int nb = (H + 1023) / 1024;
     const int b = blockIdx.x / nb;
-    const int i = (blockIdx.x % nb) * 256 + threadIdx.x;
+    const int i = (blockIdx.x % nb) * 1024 + 4 * threadIdx.x;
     const int tok = (valid == nullptr || valid[b]) ? tokens[b] : 0;
-    const float v = i < H ? bf2f(E[(size_t)tok * H + i]) : 0.f;
-    if (i < H) x[(size_t)b * H + i] = v;
+    float4 v = {0.f, 0.f, 0.f, 0.f};
+    if (i < H) {
+        const uint16_t *src = E + (size_t)tok * H + i;
+        ushort4 e;
+        if (((uintptr_t)E & 7) == 0) e = *(const ushort4 *)src;   // H % 256 == 0 keeps the rows aligned
+        else e = (ushort4){src[0], src[1], src[2], src[3]};
+        v = (float4){bf2f(e.x), bf2f(e.y), bf2f(e.z), bf2f(e.w)};
+        *(float4 *)(x + (size_t)b * H + i) = v;
+    }
     if (ss != nullptr) {
-        const float sq = row16_sum(v * v);            // lanes 16 k .. 16 k + 15: one 16-column group
-        if ((threadIdx.x & 15) == 0 && i < H) ss[(size_t)b * (H / 16) + i / 16] = sq;
+        float sq = (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
+        sq += dpp_f<0xB1>(sq);
+        sq += dpp_f<0x4E>(sq);                        // the four threads of a 16-column group
+        if ((threadIdx.x & 3) == 0 && i < H) ss[(size_t)b * (H / 16) + i / 16] = sq;
     }
 }
 
@@ -231,7 +243,7 @@ hipError_t launch_embed(const uint16_t *E, const int32_t *tokens, const uint8_t 
                         float *x, hipStream_t st, float *ss)
 {
     if (ss != nullptr && H % 256 != 0) return hipErrorInvalidValue;
-    const long long blocks = (long long)rows * ((H + 255) / 256);
+    const long long blocks = (long long)rows * ((H + 1023) / 1024);
     KLAUNCH(k_embed, dim3((unsigned)blocks), dim3(256), 0, st, E, tokens, valid, H, x, ss);
     return hipGetLastError();
 }
@@ -1313,16 +1325,18 @@ hipError_t wide_launch(dim3 grid, hipStream_t st, const uint16_t *A, int lda, co
 }
 
 // The wide tile bm x bn; false if there is none.  128 x 128 tiles that fill
-// at most one round of the 256 CUs take a ring of four stages (loads in
-// flight), more of them two stages, so that two workgroups share a CU (over
-// 24576 x 4096 at M = 8192 1654 against 1868 us).
+// at most one round of the 256 CUs, or that stream their weights for a single
+// row of tiles, take a ring of four stages (loads in flight; M = 128 over
+// 151936 x 4096: 323 against 355 us), others two stages, so that two
+// workgroups share a CU (24576 x 4096 at M = 8192: 1654 against 1868 us).
 template <int EPI, class... Args>
-bool wide_tile(int bm, int bn, hipError_t &e, dim3 grid, Args... args)
+bool wide_tile(int bm, int bn, hipError_t &e, bool one_row, dim3 grid, Args... args)
 {
     if (bm == 320 && bn == 256) e = wide_launch<320, 256, 2, 2, 8, EPI>(grid, args...);
     else if (bm == 256 && bn == 256) e = wide_launch<256, 256, 2, 2, 8, EPI>(grid, args...);
-    else if (bm == 256 && bn == 128) e = wide_launch<256, 128, 3, 2, 4, EPI>(grid, args...);
-    else if (bm == 128 && bn == 128 && grid.x * grid.y <= 256) e = wide_launch<128, 128, 4, 2, 4, EPI>(grid, args...);
+    else if (bm == 256 && bn == 128) e = wide_launch<256, 128, 3, 4, 8, EPI>(grid, args...);
+    else if (bm == 128 && bn == 128 && (one_row || grid.x * grid.y <= 256))
+        e = wide_launch<128, 128, 4, 2, 4, EPI>(grid, args...);
     else if (bm == 128 && bn == 128) e = wide_launch<128, 128, 2, 2, 4, EPI>(grid, args...);
     else return false;
     return true;
@@ -1353,7 +1367,16 @@ hipError_t launch_gemm_dma(const uint16_t *A, int lda, const uint16_t *W, const 
                 return hipErrorInvalidValue;
             return hipGetLastError();
         }
-        if (g.bm == 32 && g.bn == 128)
+        // Two workgroups with four stages (80 KB) share a CU, one with six has
+        // it alone and streams as fast; where many tiles round up badly to
+        // 512 at a time, 256 at a time wastes less of the last round
+        // (151936 x 4096: 1187 tiles are 77% of three rounds of 512 and 93%
+        // of five of 256; 222 -> 209 us at M = 1, 230 -> 216 at 16).
+        const long long n = (long long)grid.x * grid.y, r256 = (n + 255) / 256, r512 = (n + 511) / 512;
+        if (g.bm == 32 && g.bn == 128 && n > 512 && 10 * 2 * r512 > 11 * r256)
+            KLAUNCH((k_gemm_dma<32, 128, 64, 6, 1, 2, true>), grid, dim3(128), 0, st, A, lda, W, g.M, g.N,
+                               g.K, g.Kc, out, split_stride, ldo, head, nullptr, ExpertTiles{});
+        else if (g.bm == 32 && g.bn == 128)
             KLAUNCH((k_gemm_dma<32, 128, 64, 4, 1, 2, true>), grid, dim3(128), 0, st, A, lda, W, g.M, g.N,
                                g.K, g.Kc, out, split_stride, ldo, head, nullptr, ExpertTiles{});
         else if (g.bm == 64 && g.bn == 128)
@@ -1371,7 +1394,7 @@ hipError_t launch_gemm_dma(const uint16_t *A, int lda, const uint16_t *W, const 
                            out, split_stride, ldo, head, nullptr, ExpertTiles{});
     else {
         hipError_t e = hipSuccess;
-        if (wide_tile<WIDE_F32>(g.bm, g.bn, e, grid, st, A, lda, W, g.M, g.N, g.K, g.Kc, out, split_stride, ldo, head,
+        if (wide_tile<WIDE_F32>(g.bm, g.bn, e, num_m == 1, grid, st, A, lda, W, g.M, g.N, g.K, g.Kc, out, split_stride, ldo, head,
                                 (uint16_t *)nullptr, ExpertTiles{}))
             return e;
         return hipErrorInvalidValue;
@@ -1388,7 +1411,7 @@ hipError_t launch_gate_up_wide(const uint16_t *A, int lda, const uint16_t *W, co
         return hipErrorInvalidValue;
     const dim3 grid(((g.M + g.bm - 1) / g.bm) * ((g.N + g.bn - 1) / g.bn), 1);
     hipError_t e = hipSuccess;
-    if (wide_tile<WIDE_SWIGLU>(g.bm, g.bn, e, grid, st, A, lda, W, g.M, g.N, g.K, g.K, (float *)nullptr, 0ll, ldo,
+    if (wide_tile<WIDE_SWIGLU>(g.bm, g.bn, e, g.M <= g.bm, grid, st, A, lda, W, g.M, g.N, g.K, g.K, (float *)nullptr, 0ll, ldo,
                                HeadOut{}, act, ExpertTiles{}))
         return e;
     return hipErrorInvalidValue;
