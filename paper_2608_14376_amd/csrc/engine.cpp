@@ -650,6 +650,26 @@ hipError_t gate_up_swiglu(corun_engine *e, const uint16_t *A, int l, const Proj 
     return launch_gemm_dma(A, e->c.hidden, e->packed[W_GATE_UP][l], g, nullptr, 0, e->c.ffn, e->st, HeadOut{}, act);
 }
 
+// Layer l's QKV projection of a prefill over `rows` rows of pf_h, q to pf_q,
+// k and v to the cache at positions pos of slot slot_of_row (or slot_const).
+// The wide tiles without split-K apply the epilogue themselves for heads of
+// 128 (the same bits).
+corun_status prefill_qkv(corun_engine *e, int l, const Proj &pr, int rows, const int32_t *pos,
+                         const int32_t *slot_of_row, int slot_const)
+{
+    const corun_model_cfg &c = e->c;
+    const int H = c.hidden, d = c.head_dim, nq = c.n_heads, nkv = c.n_kv_heads, N = (nq + 2 * nkv) * d;
+    if (pr.bm >= 128 && pr.bn > 0 && pr.S == 1 && d == 128) {
+        const QkvOut out{e->pf_q, e->kc[l], e->vc[l], e->view, pos, slot_of_row, slot_const, nq, nkv, e->rope};
+        HIP_TRY(launch_qkv_wide(e->pf_h, H, e->w_qkv[l], shape_of(pr, rows), out, e->st));
+        return CORUN_OK;
+    }
+    HIP_TRY(proj(e, e->pf_h, H, W_QKV, l, pr, rows, e->pf_part, (long long)rows * N, N));
+    HIP_TRY(launch_qkv_post(e->pf_part, pr.S, (long long)rows * N, rows, nullptr, pos, slot_of_row, slot_const, nq, nkv,
+                            d, e->rope, e->pf_q, e->kc[l], e->vc[l], e->view, e->st));
+    return CORUN_OK;
+}
+
 // Buffers of one mixture-of-experts layer run over `rows` rows.
 struct MoeBufs {
     const uint8_t *valid;
@@ -1566,7 +1586,6 @@ extern "C" corun_status corun_prefill_chunk(corun_engine *e, const int32_t *toke
     ST_TRY(enter(e));
     const corun_model_cfg &c = e->c;
     const int H = c.hidden, d = c.head_dim, nq = c.n_heads, nkv = c.n_kv_heads, F = c.ffn;
-    const int nqkv = (nq + 2 * nkv) * d;
     hipStream_t st = e->st;
     const int Lp = n;     // rows of every projection: the chunk's tokens
     const bool bi = e->opt.batch_invariant != 0 || e->opt.bi_prefill != 0;
@@ -1582,9 +1601,7 @@ extern "C" corun_status corun_prefill_chunk(corun_engine *e, const int32_t *toke
     for (int l = 0; l < c.n_layers; ++l) {
         HIP_TRY(launch_rmsnorm(e->pf_x, l ? e->pf_part : nullptr, l ? dense_S : 0, (long long)Lp * H, Lp, H,
                                e->attn_norm[l], c.rms_eps, e->pf_h, st, fold_of(e, pmb, l)));
-        HIP_TRY(proj(e, e->pf_h, H, W_QKV, l, pq, Lp, e->pf_part, (long long)Lp * nqkv, nqkv));
-        HIP_TRY(launch_qkv_post(e->pf_part, pq.S, (long long)Lp * nqkv, Lp, nullptr, e->pf_pos + start, nullptr, slot,
-                                nq, nkv, d, e->rope, e->pf_q, e->kc[l], e->vc[l], e->view, st));
+        ST_TRY(prefill_qkv(e, l, pq, Lp, e->pf_pos + start, nullptr, slot));
         HIP_TRY(launch_prefill_attn(e->pf_q, Lp, start, nq, nkv, d, slot, e->kc[l], e->vc[l], e->view, e->pf_o, st));
         HIP_TRY(proj(e, e->pf_o, nq * d, W_O, l, po, Lp, e->pf_part, (long long)Lp * H, H));
         HIP_TRY(launch_rmsnorm(e->pf_x, e->pf_part, po.S, (long long)Lp * H, Lp, H, e->mlp_norm[l], c.rms_eps,
@@ -1673,7 +1690,6 @@ extern "C" corun_status corun_prefill_batch(corun_engine *e, const int32_t *toke
     ST_TRY(enter(e));
     const corun_model_cfg &c = e->c;
     const int H = c.hidden, d = c.head_dim, nq = c.n_heads, nkv = c.n_kv_heads, F = c.ffn;
-    const int nqkv = (nq + 2 * nkv) * d;
     const int G = nq / nkv;
     const int Lp = (int)M;   // rows of every projection: all prompts' tokens
     hipStream_t st = e->st;
@@ -1707,9 +1723,7 @@ extern "C" corun_status corun_prefill_batch(corun_engine *e, const int32_t *toke
     for (int l = 0; l < c.n_layers; ++l) {
         HIP_TRY(launch_rmsnorm(e->pf_x, l ? e->pf_part : nullptr, l ? dense_S : 0, (long long)Lp * H, Lp, H,
                                e->attn_norm[l], c.rms_eps, e->pf_h, st, fold_of(e, pmb, l)));
-        HIP_TRY(proj(e, e->pf_h, H, W_QKV, l, pq, Lp, e->pf_part, (long long)Lp * nqkv, nqkv));
-        HIP_TRY(launch_qkv_post(e->pf_part, pq.S, (long long)Lp * nqkv, Lp, nullptr, e->pf_rowpos, e->pf_rowslot, -1,
-                                nq, nkv, d, e->rope, e->pf_q, e->kc[l], e->vc[l], e->view, st));
+        ST_TRY(prefill_qkv(e, l, pq, Lp, e->pf_rowpos, e->pf_rowslot, -1));
         HIP_TRY(launch_prefill_attn_multi(e->pf_q, e->pf_seq, n, groups, nq, nkv, d, e->kc[l], e->vc[l], e->view,
                                           e->pf_o, st));
         HIP_TRY(proj(e, e->pf_o, nq * d, W_O, l, po, Lp, e->pf_part, (long long)Lp * H, H));

@@ -113,6 +113,23 @@ struct ExpertTiles {
     long long w_stride = 0;
 };
 
+struct KvView {
+    int layout;                 // 0 contiguous, 1 paged
+    int max_seq_len;            // contiguous
+    int page_size, max_pages_per_seq;
+    const int32_t *page_table;  // device
+};
+
+// Where a projection with the QKV epilogue writes: q [rows][nq 128], and k, v
+// into the cache of slot slot_of_row[r] (or slot_const) at position pos[r].
+struct QkvOut {
+    uint16_t *q = nullptr, *kc = nullptr, *vc = nullptr;
+    KvView kv{};
+    const int32_t *pos = nullptr, *slot_of_row = nullptr;
+    int slot_const = 0, nq = 0, nkv = 0;
+    const float2 *rope = nullptr;
+};
+
 struct GemmShape {
     int M, N, K;
     int S;          // split-K count
@@ -146,6 +163,11 @@ hipError_t launch_gemm_dma(const uint16_t *A, int lda, const uint16_t *W, const 
 // bits of launch_proj followed by launch_swiglu.
 hipError_t launch_gate_up_wide(const uint16_t *A, int lda, const uint16_t *W, const GemmShape &g, uint16_t *act, int ldo,
                                hipStream_t st);
+// The QKV projection with launch_qkv_post's epilogue, heads of 128, the wide
+// tile g.bm x g.bn, no split-K (K % 64 == 0): the bits of launch_proj followed
+// by launch_qkv_post over rows that are all live.
+hipError_t launch_qkv_wide(const uint16_t *A, int lda, const uint16_t *W, const GemmShape &g, const QkvOut &out,
+                           hipStream_t st);
 inline int gemm_col_blocks(int N) { return (N + 63) / 64; }
 // next[r] = host[r] (pinned host memory) = best index over the np column-block
 // partials of row r (-1 for padding rows).
@@ -156,12 +178,6 @@ hipError_t launch_copy_u32(uint32_t *dst, const uint32_t *src, int n, hipStream_
 
 // Reduce QKV partials, round to bf16, rotate q and k by their position,
 // round again, write q (bf16 [rows][nq*d]) and append k, v to the cache.
-struct KvView {
-    int layout;                 // 0 contiguous, 1 paged
-    int max_seq_len;            // contiguous
-    int page_size, max_pages_per_seq;
-    const int32_t *page_table;  // device
-};
 hipError_t launch_qkv_post(const float *part, int S, long long part_stride, int rows,
                            const uint8_t *valid, const int32_t *pos, const int32_t *slot_of_row,
                            int slot_const, int nq, int nkv, int d, const float2 *rope_tab,

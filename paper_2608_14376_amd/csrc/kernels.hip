@@ -105,12 +105,16 @@ __device__ __forceinline__ float wave_max(float v)
     return v;
 }
 
+// Row of a paged cache, d elements each, that holds token t of a slot's kv head.
+__device__ __forceinline__ size_t kv_row_paged(const KvView &kv, int nkv, int slot, int kvh, int t)
+{
+    const int page = kv.page_table[(size_t)slot * kv.max_pages_per_seq + t / kv.page_size];
+    return ((size_t)page * nkv + kvh) * kv.page_size + (t % kv.page_size);
+}
+
 __device__ __forceinline__ size_t kv_offset(const KvView &kv, int nkv, int d, int slot, int kvh, int t)
 {
-    if (kv.layout == 1) {
-        int page = kv.page_table[(size_t)slot * kv.max_pages_per_seq + t / kv.page_size];
-        return (((size_t)page * nkv + kvh) * kv.page_size + (t % kv.page_size)) * d;
-    }
+    if (kv.layout == 1) return kv_row_paged(kv, nkv, slot, kvh, t) * d;
     return (((size_t)slot * nkv + kvh) * kv.max_seq_len + t) * d;
 }
 
@@ -1029,6 +1033,11 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_dma(const uint16_t *__restrict
 // [M][2F] sums never reach memory (at M = 32768 over 24576 x 4096 they cost
 // 3.2 GB written and read again).
 //
+// QKV epilogue (EPI 2, heads of 128): the same pairing inside a head, columns
+// i and i + 64, so each lane rotates its own pair and writes q and the cache.
+// Projection and separate kernel, 6144 x 4096: 1357 + 397 us at M = 32768, 197 +
+// 49 at 4200, 40 + 10 at 600; now 1487, 215 and 46.
+//
 // Tile order: with several M tiles, workgroups are handed to the eight XCDs
 // in turn, so each XCD gets a contiguous run of tiles, walked in groups of
 // eight M tiles per N tile: the workgroups sharing a weight tile or an
@@ -1037,14 +1046,32 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_dma(const uint16_t *__restrict
 // MOE: grid.y walks the expert tile slots of up to BM assignments (as in
 // k_gemm_dma).  PKW: W is the tile-packed copy.
 // ---------------------------------------------------------------------------
-enum { WIDE_F32 = 0, WIDE_SWIGLU = 1 };
+enum { WIDE_F32 = 0, WIDE_SWIGLU = 1, WIDE_QKV = 2 };
+
+// q and k of one rotation pair (columns i and i + d / 2 of a head) or two
+// values of v, from their fp32 sums: rounded to bf16, rotated by (cos, sin)
+// when rot, rounded again.  Every QKV epilogue runs this, so all write the
+// same bits.
+__device__ __forceinline__ void qkv_round(float x0, float x1, bool rot, float2 cs, uint16_t &b0, uint16_t &b1)
+{
+    x0 = bf2f(f2bf(x0));
+    x1 = bf2f(f2bf(x1));
+    if (rot) {
+        const float y0 = __builtin_fmaf(x0, cs.x, -(x1 * cs.y));
+        const float y1 = __builtin_fmaf(x1, cs.x, x0 * cs.y);
+        x0 = y0;
+        x1 = y1;
+    }
+    b0 = f2bf(x0);
+    b1 = f2bf(x1);
+}
 
 template <int BM, int BN, int NST, int WGM, int NW, int EPI, bool MOE = false, bool PKW = false>
 __global__ __launch_bounds__(64 * NW) void k_gemm_wide(const uint16_t *__restrict__ A, int lda,
                                                        const uint16_t *__restrict__ W, int M, int N, int K, int Kc,
                                                        float *__restrict__ out, long long split_stride, int ldo,
                                                        HeadOut head, uint16_t *__restrict__ act,
-                                                       ExpertTiles et)
+                                                       ExpertTiles et, QkvOut qo)
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // buffer resources exist in device code only
     constexpr int BK = 64, C = BK / 8;                // 16-byte chunks per row
@@ -1158,8 +1185,8 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_wide(const uint16_t *__restric
     const int wm0 = (wave / WGN) * WM, wn0 = wn * WN;
     const int r32 = lane & 31, h = lane >> 5;
     // the wavefront's first W row in the tile, and its second fragment's distance
-    const int wrow0 = EPI == WIDE_SWIGLU ? 128 * (wn >> 1) + 32 * (wn & 1) : wn0;
-    constexpr int WFRAG = EPI == WIDE_SWIGLU ? 64 : 32;
+    const int wrow0 = EPI != WIDE_F32 ? 128 * (wn >> 1) + 32 * (wn & 1) : wn0;
+    constexpr int WFRAG = EPI != WIDE_F32 ? 64 : 32;
     struct Frags {
         bf16x8 a[FM], w[FN];
     };
@@ -1260,6 +1287,51 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_wide(const uint16_t *__restric
                         act[out_row(row) * ldo + j] = swiglu_bf16(0.f + acc[a][0][q], 0.f + acc[a][1][q]);
                 }
         return;
+    } else if constexpr (EPI == WIDE_QKV) {
+        constexpr int D = 128;
+        const int hd = n0 / D + (wn >> 1), i = 32 * (wn & 1) + r32;   // the wavefront's head; pair (i, i + 64)
+        if (hd >= qo.nq + 2 * qo.nkv) return;
+        const bool rot = hd < qo.nq + qo.nkv;
+        const bool full = m0 + BM <= M;
+        uint16_t *base = (hd < qo.nq ? qo.q : rot ? qo.kc : qo.vc) + i;
+        const int kvh = hd - (rot ? qo.nq : qo.nq + qo.nkv);
+        // eight rows at a time: their loads together, then the rotations and stores
+#pragma unroll
+        for (int a8 = 0; a8 < 2 * FM; ++a8) {
+            const int a = a8 >> 1, q0 = 8 * (a8 & 1);
+            auto row_of = [&](int q) { return m0 + wm0 + 32 * a + 4 * h + 8 * ((q0 + q) >> 2) + (q & 3); };
+            int p[8];
+            float2 cs[8];
+            uint32_t at[8];                           // row of q or of the cache, in heads of D
+#pragma unroll
+            for (int q = 0; q < 8; ++q) p[q] = qo.pos[min(row_of(q), M - 1)];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) cs[q] = rot ? qo.rope[(size_t)p[q] * (D / 2) + i] : make_float2(1.f, 0.f);
+            if (hd < qo.nq) {
+#pragma unroll
+                for (int q = 0; q < 8; ++q) at[q] = (uint32_t)(row_of(q) * qo.nq + hd);
+            } else {
+                int slot[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) slot[q] = row_slot(qo.slot_of_row, qo.slot_const, min(row_of(q), M - 1));
+                if (qo.kv.layout == 1) {
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) at[q] = (uint32_t)kv_row_paged(qo.kv, qo.nkv, slot[q], kvh, p[q]);
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) at[q] = (uint32_t)(slot[q] * qo.nkv + kvh) * (uint32_t)qo.kv.max_seq_len + (uint32_t)p[q];
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                if (!full && row_of(q) >= M) continue;
+                uint16_t b0, b1;
+                qkv_round(0.f + acc[a][0][q0 + q], 0.f + acc[a][1][q0 + q], rot, cs[q], b0, b1);
+                uint16_t *dst = base + (size_t)at[q] * D;
+                dst[0] = b0;
+                dst[64] = b1;
+            }
+        }
     } else {
         float *o = head_out(head, out) + (size_t)s * split_stride;
 #pragma unroll
@@ -1318,9 +1390,9 @@ namespace {
 template <int BM, int BN, int NST, int WGM, int NW, int EPI, bool MOE = false, bool PKW = false>
 hipError_t wide_launch(dim3 grid, hipStream_t st, const uint16_t *A, int lda, const uint16_t *W, int M, int N, int K,
                        int Kc, float *out, long long split_stride, int ldo, HeadOut head, uint16_t *act,
-                       ExpertTiles et)
+                       ExpertTiles et, QkvOut qo = QkvOut{})
 {
-    KLAUNCH((k_gemm_wide<BM, BN, NST, WGM, NW, EPI, MOE, PKW>), grid, dim3(64 * NW), 0, st, A, lda, W, M, N, K, Kc, out, split_stride, ldo, head, act, et);
+    KLAUNCH((k_gemm_wide<BM, BN, NST, WGM, NW, EPI, MOE, PKW>), grid, dim3(64 * NW), 0, st, A, lda, W, M, N, K, Kc, out, split_stride, ldo, head, act, et, qo);
     return hipGetLastError();
 }
 
@@ -1417,6 +1489,18 @@ hipError_t launch_gate_up_wide(const uint16_t *A, int lda, const uint16_t *W, co
     return hipErrorInvalidValue;
 }
 
+hipError_t launch_qkv_wide(const uint16_t *A, int lda, const uint16_t *W, const GemmShape &g, const QkvOut &out,
+                           hipStream_t st)
+{
+    if (g.K % 64 != 0 || g.S != 1 || g.M <= 0 || g.N != (out.nq + 2 * out.nkv) * 128) return hipErrorInvalidValue;
+    const dim3 grid(((g.M + g.bm - 1) / g.bm) * ((g.N + g.bn - 1) / g.bn), 1);
+    hipError_t e = hipSuccess;
+    if (wide_tile<WIDE_QKV>(g.bm, g.bn, e, g.M <= g.bm, grid, st, A, lda, W, g.M, g.N, g.K, g.K, (float *)nullptr, 0ll, 0,
+                            HeadOut{}, (uint16_t *)nullptr, ExpertTiles{}, out))
+        return e;
+    return hipErrorInvalidValue;
+}
+
 hipError_t launch_gemm_tiled(const uint16_t *A, int lda, const uint16_t *W, const GemmShape &g, int bm, float *out,
                              long long split_stride, int ldo, hipStream_t st, HeadOut head)
 {
@@ -1501,16 +1585,7 @@ __device__ __forceinline__ void qkv_pair(const float *__restrict__ pb, long long
                 x1 += a1[u];
             }
     }
-    x0 = bf2f(f2bf(x0));
-    x1 = bf2f(f2bf(x1));
-    if (rot) {
-        const float y0 = __builtin_fmaf(x0, cs.x, -(x1 * cs.y));
-        const float y1 = __builtin_fmaf(x1, cs.x, x0 * cs.y);
-        x0 = y0;
-        x1 = y1;
-    }
-    b0 = f2bf(x0);
-    b1 = f2bf(x1);
+    qkv_round(x0, x1, rot, cs, b0, b1);
 }
 
 __global__ void k_qkv_post(const float *__restrict__ part, int S, long long part_stride,
