@@ -829,6 +829,19 @@ hipError_t gemv_proj(corun_engine *e, int which, int l)
     }
 }
 
+// The decode step's tokens, with fb also its feedback (an unsplit lm_head's
+// argmax only).
+corun_status argmax(corun_engine *e, const StepFeedback &fb)
+{
+    const Plan &p = e->plan;
+    if (p.lm.S == 1)
+        HIP_TRY(launch_argmax_partials(e->amax, e->B, gemm_col_blocks(e->c.vocab), e->d_valid, e->d_next, e->h_next,
+                                       e->st, fb));
+    else
+        HIP_TRY(launch_argmax(e->logits, e->B, e->c.vocab, e->d_valid, e->d_next, e->st));
+    return CORUN_OK;
+}
+
 // One kernel of layer l of the decode step; the step is these in order.
 corun_status launch_one(corun_engine *e, int which, int l)
 {
@@ -916,10 +929,7 @@ corun_status launch_one(corun_engine *e, int which, int l)
         }
         break;
     case CORUN_K_ARGMAX:
-        if (p.lm.S == 1)
-            HIP_TRY(launch_argmax_partials(e->amax, B, gemm_col_blocks(c.vocab), e->d_valid, e->d_next, e->h_next, st));
-        else
-            HIP_TRY(launch_argmax(e->logits, B, c.vocab, e->d_valid, e->d_next, st));
+        ST_TRY(argmax(e, StepFeedback{}));
         break;
     default:
         return fail(CORUN_E_INVAL, "unknown kernel id %d", which);
@@ -957,9 +967,10 @@ corun_status enqueue_step(corun_engine *e)
     const Plan &p = e->plan;
     const int B = e->B, H = c.hidden;
     hipStream_t st = e->st;
-    const int OTHER = CORUN_K_COUNT;   // embedding and feedback
+    const int OTHER = CORUN_K_COUNT;   // embedding (and a split lm_head's feedback)
     ST_TRY(timed(e, OTHER, [&]() -> corun_status {
-        HIP_TRY(launch_embed(e->embed, e->d_tokens, e->d_valid, B, H, e->x, st, p.gv ? e->gss : nullptr));
+        HIP_TRY(launch_embed(e->embed, e->d_tokens, e->d_valid, B, H, e->x, st, p.gv ? e->gss : nullptr,
+                             e->d_counter));
         return CORUN_OK;
     }));
     const MoeBufs mb = decode_moe(e);
@@ -984,12 +995,14 @@ corun_status enqueue_step(corun_engine *e)
         return CORUN_OK;
     }));
     ST_TRY(timed(e, CORUN_K_LM_HEAD, [&] { return launch_one(e, CORUN_K_LM_HEAD, 0); }));
-    ST_TRY(timed(e, CORUN_K_ARGMAX, [&] { return launch_one(e, CORUN_K_ARGMAX, 0); }));
-    ST_TRY(timed(e, OTHER, [&]() -> corun_status {
-        HIP_TRY(launch_feedback(e->d_tokens, e->d_seq, e->d_valid, e->d_next, B, e->d_hist, e->d_counter,
-                                e->hist_cap, st));
-        return CORUN_OK;
-    }));
+    // the step's feedback rides on the argmax (a launch of its own cost 4 us)
+    const StepFeedback fb{e->d_tokens, e->d_seq, e->d_hist, e->d_counter, e->hist_cap};
+    ST_TRY(timed(e, CORUN_K_ARGMAX, [&] { return argmax(e, fb); }));
+    if (p.lm.S > 1)
+        ST_TRY(timed(e, OTHER, [&]() -> corun_status {
+            HIP_TRY(launch_feedback(e->d_next, B, e->d_valid, fb, st));
+            return CORUN_OK;
+        }));
     return CORUN_OK;
 }
 

@@ -26,9 +26,10 @@ void set_launch_recorder(LaunchRecorder *r);
 
 // Per-row token selection and fp32 residual init: x[b] = float(E[tok_b]),
 // tok_b = valid[b] ? tokens[b] : 0; with ss, also the sums of squares of x[b]
-// over 16-column groups, ss[b][H / 16] (launch_gemv's norm input).
+// over 16-column groups, ss[b][H / 16] (launch_gemv's norm input).  With
+// counter, *counter += 1: the step's StepFeedback index is *counter - 1.
 hipError_t launch_embed(const uint16_t *E, const int32_t *tokens, const uint8_t *valid, int rows,
-                        int H, float *x, hipStream_t st, float *ss = nullptr);
+                        int H, float *x, hipStream_t st, float *ss = nullptr, int32_t *counter = nullptr);
 
 // Mixture-of-experts combine folded into the next RMSNorm:
 // x[b] += sum_{r < top_k} w[b][r] y[b top_k + r] (rank order) for valid rows.
@@ -169,10 +170,19 @@ hipError_t launch_gate_up_wide(const uint16_t *A, int lda, const uint16_t *W, co
 hipError_t launch_qkv_wide(const uint16_t *A, int lda, const uint16_t *W, const GemmShape &g, const QkvOut &out,
                            hipStream_t st);
 inline int gemm_col_blocks(int N) { return (N + 63) / 64; }
+// Device-side feedback between replayed steps: live rows take their next
+// token and advance their position; the step's tokens are appended to the
+// history at step index *counter - 1 (launch_embed counts the steps; nothing is
+// appended from index max_hist on).
+struct StepFeedback {
+    int32_t *tokens = nullptr, *seq_lens = nullptr, *history = nullptr;
+    const int32_t *counter = nullptr;   // nullptr: no feedback
+    int max_hist = 0;
+};
 // next[r] = host[r] (pinned host memory) = best index over the np column-block
 // partials of row r (-1 for padding rows).
 hipError_t launch_argmax_partials(const ArgBest *part, int rows, int np, const uint8_t *valid, int32_t *next,
-                                  int32_t *host, hipStream_t st);
+                                  int32_t *host, hipStream_t st, const StepFeedback &fb = StepFeedback{});
 // n words from pinned host memory, in one workgroup.
 hipError_t launch_copy_u32(uint32_t *dst, const uint32_t *src, int n, hipStream_t st);
 
@@ -247,12 +257,8 @@ hipError_t launch_reduce_splits(const float *part, int S, long long stride, long
 hipError_t launch_argmax(const float *logits, int rows, int V, const uint8_t *valid, int32_t *next,
                          hipStream_t st);
 
-// Device-side feedback between replayed steps: live rows take their next
-// token and advance their position; the step's tokens are appended to the
-// history at step index *counter, which then increments.
-hipError_t launch_feedback(int32_t *tokens, int32_t *seq_lens, const uint8_t *valid,
-                           const int32_t *next, int B, int32_t *history, int32_t *counter,
-                           int max_hist, hipStream_t st);
+// The feedback of tokens next [B] on its own (launch_argmax's).
+hipError_t launch_feedback(const int32_t *next, int B, const uint8_t *valid, const StepFeedback &fb, hipStream_t st);
 
 // cos / sin table of the rotary embedding: tab[p][i] = (cos, sin)(p * theta^(-2i/d))
 // evaluated in fp64 and rounded to fp32.

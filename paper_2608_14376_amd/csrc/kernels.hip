@@ -217,11 +217,13 @@ __device__ __forceinline__ float wave_sum_dpp(float v)
 // copies four elements (one element per thread took 371 us for 32768 rows of
 // 4096, bound by the number of workgroups).  With ss (H a multiple of 256) it
 // also writes each row's sums of squares over 16-column groups, ss[b][i / 16],
-// for the small-batch projections' norm: four threads' 4-element sums.
+// for the small-batch projections' norm: four threads' 4-element sums; with
+// counter, one thread counts the step begun (k_argmax_partials' feedback).
 __global__ __launch_bounds__(256) void k_embed(const uint16_t *__restrict__ E, const int32_t *__restrict__ tokens,
                                                const uint8_t *__restrict__ valid, int H, float *__restrict__ x,
-                                               float *__restrict__ ss)
+                                               float *__restrict__ ss, int32_t *__restrict__ counter)
 {
+    if (counter != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *counter += 1;
     const int nb = (H + 1023) / 1024;
     const int b = blockIdx.x / nb;
     const int i = (blockIdx.x % nb) * 1024 + 4 * threadIdx.x;
@@ -244,11 +246,11 @@ __global__ __launch_bounds__(256) void k_embed(const uint16_t *__restrict__ E, c
 }
 
 hipError_t launch_embed(const uint16_t *E, const int32_t *tokens, const uint8_t *valid, int rows, int H,
-                        float *x, hipStream_t st, float *ss)
+                        float *x, hipStream_t st, float *ss, int32_t *counter)
 {
     if (ss != nullptr && H % 256 != 0) return hipErrorInvalidValue;
     const long long blocks = (long long)rows * ((H + 1023) / 1024);
-    KLAUNCH(k_embed, dim3((unsigned)blocks), dim3(256), 0, st, E, tokens, valid, H, x, ss);
+    KLAUNCH(k_embed, dim3((unsigned)blocks), dim3(256), 0, st, E, tokens, valid, H, x, ss, counter);
     return hipGetLastError();
 }
 
@@ -2332,15 +2334,27 @@ __global__ __launch_bounds__(256) void k_argmax(const float *__restrict__ logits
     }
 }
 
+// Row r's part of the feedback (StepFeedback).
+__device__ __forceinline__ void step_feedback(const StepFeedback &fb, bool live, int r, int rows, int next)
+{
+    const int c = *fb.counter - 1;                    // this step's index
+    if (c < fb.max_hist) fb.history[(size_t)c * rows + r] = next;
+    if (live) {
+        fb.tokens[r] = next;
+        fb.seq_lens[r] += 1;
+    }
+}
+
 __global__ __launch_bounds__(256) void k_argmax_partials(const ArgBest *__restrict__ part, int np,
                                                          const uint8_t *__restrict__ valid, int32_t *__restrict__ next,
-                                                         int32_t *__restrict__ host)
+                                                         int32_t *__restrict__ host, StepFeedback fb)
 {
     const int r = blockIdx.x;
     if (valid != nullptr && !valid[r]) {
         if (threadIdx.x == 0) {
             next[r] = -1;
             host[r] = -1;
+            if (fb.counter != nullptr) step_feedback(fb, false, r, gridDim.x, -1);
         }
         return;
     }
@@ -2366,13 +2380,14 @@ __global__ __launch_bounds__(256) void k_argmax_partials(const ArgBest *__restri
         const int best = (bi == 0x7fffffff) ? 0 : bi;
         next[r] = best;
         host[r] = best;
+        if (fb.counter != nullptr) step_feedback(fb, true, r, gridDim.x, best);
     }
 }
 
 hipError_t launch_argmax_partials(const ArgBest *part, int rows, int np, const uint8_t *valid, int32_t *next,
-                                  int32_t *host, hipStream_t st)
+                                  int32_t *host, hipStream_t st, const StepFeedback &fb)
 {
-    KLAUNCH(k_argmax_partials, dim3(rows), dim3(256), 0, st, part, np, valid, next, host);
+    KLAUNCH(k_argmax_partials, dim3(rows), dim3(256), 0, st, part, np, valid, next, host, fb);
     return hipGetLastError();
 }
 
@@ -2385,26 +2400,14 @@ hipError_t launch_argmax(const float *logits, int rows, int V, const uint8_t *va
 // ---------------------------------------------------------------------------
 // Device-side step feedback for multi-step runs.
 // ---------------------------------------------------------------------------
-__global__ void k_feedback(int32_t *tokens, int32_t *seq_lens, const uint8_t *valid, const int32_t *next, int B,
-                           int32_t *history, int32_t *counter, int max_hist)
+__global__ void k_feedback(const int32_t *__restrict__ next, int B, const uint8_t *__restrict__ valid, StepFeedback fb)
 {
-    const int c = *counter;
-    for (int b = threadIdx.x; b < B; b += blockDim.x) {
-        if (c < max_hist) history[(size_t)c * B + b] = next[b];
-        if (valid[b]) {
-            tokens[b] = next[b];
-            seq_lens[b] += 1;
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) *counter = c + 1;
+    for (int b = threadIdx.x; b < B; b += blockDim.x) step_feedback(fb, valid[b], b, B, next[b]);
 }
 
-hipError_t launch_feedback(int32_t *tokens, int32_t *seq_lens, const uint8_t *valid, const int32_t *next, int B,
-                           int32_t *history, int32_t *counter, int max_hist, hipStream_t st)
+hipError_t launch_feedback(const int32_t *next, int B, const uint8_t *valid, const StepFeedback &fb, hipStream_t st)
 {
-    KLAUNCH(k_feedback, dim3(1), dim3(256), 0, st, tokens, seq_lens, valid, next, B, history, counter,
-                       max_hist);
+    KLAUNCH(k_feedback, dim3(1), dim3(256), 0, st, next, B, valid, fb);
     return hipGetLastError();
 }
 
