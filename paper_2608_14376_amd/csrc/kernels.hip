@@ -3243,12 +3243,13 @@ __device__ __forceinline__ int pf_swz(int r, int c)
 }
 
 // One workgroup of the kernel: kv head kvh, unit group grp of one prompt.
-template <int D>
+template <int D, bool ANY>
 __device__ __forceinline__ void prefill_attn_block(const uint16_t *__restrict__ q, int n, int p0, int nq, int nkv,
                                                    int slot, const uint16_t *__restrict__ kc,
                                                    const uint16_t *__restrict__ vc, const KvView &kv,
                                                    uint16_t *__restrict__ o, int kvh, int grp)
 {
+#if defined(__HIP_DEVICE_COMPILE__)   // buffer resources exist in device code only
     constexpr int NW = 8, NT = 64 * NW;              // wavefronts, threads
     constexpr int QB = 32, BKT = 64;                  // queries per wavefront, keys per tile
     constexpr int DT = D / 32, KS = D / 16;           // 32-dim output tiles, 16-dim score steps
@@ -3269,7 +3270,8 @@ __device__ __forceinline__ void prefill_attn_block(const uint16_t *__restrict__ 
     const int Lk = p0 + n;
     // grid (kv head, unit group): workgroups are dispatched x fastest, so the
     // groups with the latest (longest) query blocks of every kv head go first
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: scalar branches and addresses
     const int r32 = lane & 31, h = lane >> 5;
     const int nqb = (n + QB - 1) / QB;
     const int units = nqb * G;
@@ -3286,8 +3288,32 @@ __device__ __forceinline__ void prefill_attn_block(const uint16_t *__restrict__ 
     // tile loads: op j of thread t is 16-byte unit 512 j + t of the K part
     // or of the V part (token-major both, row = unit / KCH)
     typedef __attribute__((address_space(3))) void lds_void;
+    // ANY: any layout, an address per row.  Otherwise contiguous rows within
+    // 2 GiB: the (slot, kv head)'s rows through buffer resources, the
+    // tile's offset in a scalar register.  (Global loads to LDS also cost the
+    // LDS reads their partial waits: the compiler waits for all of them.)
+    // A tile past the last loads the last one again.
+    const size_t row0 = ANY ? 0 : kv_offset(kv, nkv, D, slot, kvh, 0);
+    const auto rk = __builtin_amdgcn_make_buffer_rsrc((void *)(kc + row0), 0, 0xFFFFFFFF, 0x00020000);
+    const auto rv = __builtin_amdgcn_make_buffer_rsrc((void *)(vc + row0), 0, 0xFFFFFFFF, 0x00020000);
     auto issue = [&](int slot_, int k0) {
         uint4 *base = ring + slot_ * STAGE + wave * 64;
+        if constexpr (!ANY) {
+            const int kb = min(k0, (Lk - 1) / BKT * BKT), top = Lk - 1 - kb;
+#pragma unroll
+            for (int j = 0; j < K_OPS; ++j) {
+                const int gi = j * NT + tid, r = gi / KCH, c = pf_swz<KCH>(r, gi % KCH) - r * KCH;
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (lds_void *)(base + j * NT), 16, (min(r, top) * D + 8 * c) * 2,
+                                                         kb * D * 2, 0, 0);
+            }
+#pragma unroll
+            for (int j = 0; j < V_OPS; ++j) {
+                const int gi = j * NT + tid, r = gi / KCH, c = (gi % KCH) ^ vtile_swz<KCH>(r);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (lds_void *)(base + KSTAGE + j * NT), 16,
+                                                         (min(r, top) * D + 8 * c) * 2, kb * D * 2, 0, 0);
+            }
+            return;
+        }
 #pragma unroll
         for (int j = 0; j < K_OPS; ++j) {
             const int gi = j * NT + tid, r = gi / KCH, c = pf_swz<KCH>(r, gi % KCH) - r * KCH;
@@ -3337,7 +3363,9 @@ __device__ __forceinline__ void prefill_attn_block(const uint16_t *__restrict__ 
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(P * OPS));
     for (int i = 0; i < ntiles; ++i) {
         wait_stages<OPS, P - 1>(min(P - 1, ntiles - 1 - i));
+        __builtin_amdgcn_s_waitcnt(0xC07F);           // lgkmcnt(0): the previous tile's reads, whose slot is refilled below
         lds_barrier();
+        __builtin_amdgcn_sched_barrier(0);
         const int k0 = i * BKT;
         uint4 *Kt = ring + (i % NST) * STAGE;
         uint4 *Vt = Kt + KSTAGE;
@@ -3356,13 +3384,30 @@ __device__ __forceinline__ void prefill_attn_block(const uint16_t *__restrict__ 
         for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
             for (int j = 0; j < 16; ++j) st[kt][j] = 0.f;
+        // Key operands KD steps ahead of their products, in a fixed order: left
+        // to itself the compiler read a step's two operands into the registers
+        // of the last and waited for them in front of every product pair (2048
+        // queries at 14336: 602 -> 562 us with the buffer loads above; KD = 3,
+        // or a raised wavefront priority over the products, no faster).
+        constexpr int KD = 2;
+        bf16x8 kf[KD + 1][2];
+        auto kread = [&](int ks) {
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
+            for (int kt = 0; kt < 2; ++kt)
+                kf[ks % (KD + 1)][kt] =
+                    __builtin_bit_cast(bf16x8, Kt[pf_swz<KCH>(32 * kt + pf_key_of_row(r32), 2 * ks + h)]);
+        };
 #pragma unroll
-            for (int kt = 0; kt < 2; ++kt) {
-                const bf16x8 kf = __builtin_bit_cast(bf16x8, Kt[pf_swz<KCH>(32 * kt + pf_key_of_row(r32), 2 * ks + h)]);
-                st[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], st[kt], 0, 0, 0);
-            }
+        for (int ks = 0; ks < KD; ++ks) kread(ks);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            if (ks + KD < KS) kread(ks + KD);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt)
+                st[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks % (KD + 1)][kt], qf[ks], st[kt], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
         // online softmax in base 2; lane holds keys k0 + 32 kt + 16 (j / 8) + 8 h + j % 8
         // of query qq; only tiles reaching past the wavefront's first query or
         // past the prompt need the mask
@@ -3462,15 +3507,16 @@ __device__ __forceinline__ void prefill_attn_block(const uint16_t *__restrict__ 
         if (qo < n)
             *(uint4 *)(o + (size_t)qo * nq * D + (size_t)hq * D + 8 * c8) = *(const uint4 *)(ost + qr * OPITCH + 8 * c8);
     }
+#endif
 }
 
-template <int D>
+template <int D, bool ANY>
 __global__ __launch_bounds__(512) void k_prefill_attn(const uint16_t *__restrict__ q, int n, int p0, int nq, int nkv,
                                                       int slot, const uint16_t *__restrict__ kc,
                                                       const uint16_t *__restrict__ vc, KvView kv,
                                                       uint16_t *__restrict__ o)
 {
-    prefill_attn_block<D>(q, n, p0, nq, nkv, slot, kc, vc, kv, o, blockIdx.x, blockIdx.y);
+    prefill_attn_block<D, ANY>(q, n, p0, nq, nkv, slot, kc, vc, kv, o, blockIdx.x, blockIdx.y);
 }
 
 // Several prompts in one launch (batched prefill): prompt i owns rows
@@ -3478,7 +3524,7 @@ __global__ __launch_bounds__(512) void k_prefill_attn(const uint16_t *__restrict
 // groups of all prompts follow one another along the grid's y, prompt i's
 // starting at seq[i].grp0.  Each workgroup runs exactly the arithmetic of the
 // same unit in the prompt's own launch.
-template <int D>
+template <int D, bool ANY>
 __global__ __launch_bounds__(512) void k_prefill_attn_multi(const uint16_t *__restrict__ q,
                                                             const int32_t *__restrict__ seq, int nseq, int nq,
                                                             int nkv, const uint16_t *__restrict__ kc,
@@ -3490,7 +3536,14 @@ __global__ __launch_bounds__(512) void k_prefill_attn_multi(const uint16_t *__re
     while (i + 1 < nseq && seq[4 * (i + 1) + 3] <= g) ++i;
     const int row0 = seq[4 * i], len = seq[4 * i + 1], slot = seq[4 * i + 2], grp = g - seq[4 * i + 3];
     const size_t ofs = (size_t)row0 * nq * D;
-    prefill_attn_block<D>(q + ofs, len, 0, nq, nkv, slot, kc, vc, kv, o + ofs, blockIdx.x, grp);
+    prefill_attn_block<D, ANY>(q + ofs, len, 0, nq, nkv, slot, kc, vc, kv, o + ofs, blockIdx.x, grp);
+}
+
+// Whether a (slot, kv head)'s rows need an address each: paged, or rows past
+// the 31-bit offsets of the buffer loads.
+static bool pf_any_layout(const KvView &kv, int d)
+{
+    return kv.layout == 1 || (long long)kv.max_seq_len * d * 2 >= (1ll << 31);
 }
 
 hipError_t launch_prefill_attn_multi(const uint16_t *q, const int32_t *seq, int nseq, int total_groups, int nq,
@@ -3499,10 +3552,15 @@ hipError_t launch_prefill_attn_multi(const uint16_t *q, const int32_t *seq, int 
 {
     if (nseq <= 0 || total_groups <= 0) return hipErrorInvalidValue;
     dim3 grid(nkv, total_groups);
-    if (d == 128)
-        KLAUNCH((k_prefill_attn_multi<128>), grid, dim3(512), 0, st, q, seq, nseq, nq, nkv, kc, vc, kv, o);
+    const bool any = pf_any_layout(kv, d);
+    if (d == 128 && any)
+        KLAUNCH((k_prefill_attn_multi<128, true>), grid, dim3(512), 0, st, q, seq, nseq, nq, nkv, kc, vc, kv, o);
+    else if (d == 128)
+        KLAUNCH((k_prefill_attn_multi<128, false>), grid, dim3(512), 0, st, q, seq, nseq, nq, nkv, kc, vc, kv, o);
+    else if (d == 64 && any)
+        KLAUNCH((k_prefill_attn_multi<64, true>), grid, dim3(512), 0, st, q, seq, nseq, nq, nkv, kc, vc, kv, o);
     else if (d == 64)
-        KLAUNCH((k_prefill_attn_multi<64>), grid, dim3(512), 0, st, q, seq, nseq, nq, nkv, kc, vc, kv, o);
+        KLAUNCH((k_prefill_attn_multi<64, false>), grid, dim3(512), 0, st, q, seq, nseq, nq, nkv, kc, vc, kv, o);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();
@@ -3533,10 +3591,15 @@ hipError_t launch_prefill_attn(const uint16_t *q, int n, int p0, int nq, int nkv
     const int G = nq / nkv;
     const int units = ((n + 31) / 32) * G;
     dim3 grid(nkv, (units + 7) / 8);
-    if (d == 128)
-        KLAUNCH((k_prefill_attn<128>), grid, dim3(512), 0, st, q, n, p0, nq, nkv, slot, kc, vc, kv, o);
+    const bool any = pf_any_layout(kv, d);
+    if (d == 128 && any)
+        KLAUNCH((k_prefill_attn<128, true>), grid, dim3(512), 0, st, q, n, p0, nq, nkv, slot, kc, vc, kv, o);
+    else if (d == 128)
+        KLAUNCH((k_prefill_attn<128, false>), grid, dim3(512), 0, st, q, n, p0, nq, nkv, slot, kc, vc, kv, o);
+    else if (d == 64 && any)
+        KLAUNCH((k_prefill_attn<64, true>), grid, dim3(512), 0, st, q, n, p0, nq, nkv, slot, kc, vc, kv, o);
     else if (d == 64)
-        KLAUNCH((k_prefill_attn<64>), grid, dim3(512), 0, st, q, n, p0, nq, nkv, slot, kc, vc, kv, o);
+        KLAUNCH((k_prefill_attn<64, false>), grid, dim3(512), 0, st, q, n, p0, nq, nkv, slot, kc, vc, kv, o);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();
