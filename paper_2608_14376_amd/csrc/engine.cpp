@@ -337,6 +337,7 @@ struct corun_engine {
     Plan plan;
     hipStream_t user = nullptr, st = nullptr;
     hipEvent_t ev = nullptr;
+    int device = 0;          // the current device at creation
 
     const uint16_t *embed = nullptr, *final_norm = nullptr, *lm_head = nullptr;
     std::vector<const uint16_t *> attn_norm, w_qkv, w_o, mlp_norm, w_gu, w_down, w_router, w_egu, w_edown;
@@ -1395,7 +1396,7 @@ extern "C" corun_status corun_engine_create(const corun_model_cfg *cfg, const co
     cv.take(&e->a, (size_t)p.Mp * F);
     size_t total = cv.take(&e->rope, (size_t)rope_len * (d / 2));
     e->ws_bytes = total;
-    if (hipMalloc(&e->ws, total) != hipSuccess) return bail(fail(CORUN_E_HIP, "workspace allocation of %zu bytes", total));
+    if (hipGetDevice(&e->device) != hipSuccess || hipMalloc(&e->ws, total) != hipSuccess) return bail(fail(CORUN_E_HIP, "workspace allocation of %zu bytes", total));
     rebase(e->d_in, e->ws);
     e->d_tokens = reinterpret_cast<int32_t *>(e->d_in);
     e->d_seq = e->d_tokens + in.seq;
@@ -1477,6 +1478,16 @@ extern "C" void corun_engine_destroy(corun_engine *e)
 // Decode
 // ---------------------------------------------------------------------------
 
+// Whether kernels on the engine's device may write to the buffer: device
+// memory of that device.  (Others are filled by a copy, as any buffer once was.)
+static bool device_buffer(const corun_engine *e, const void *p)
+{
+    hipPointerAttribute_t a{};
+    if (hipPointerGetAttributes(&a, p) == hipSuccess) return a.type == hipMemoryTypeDevice && a.device == e->device;
+    (void)hipGetLastError();
+    return false;
+}
+
 // The step's inputs to the device, `logits` the address its logits go to
 // (nullptr: the engine's own buffer).
 static corun_status upload_inputs(corun_engine *e, const int32_t *tokens, const uint8_t *valid,
@@ -1519,13 +1530,13 @@ extern "C" corun_status corun_decode_step(corun_engine *e, const int32_t *tokens
     ST_TRY(check_pages(e, seq_lens, valid, tokens, e->B, 1));
     ST_TRY(enter(e));
     // an unsplit lm_head (every plan but the split-K test aid's) writes the
-    // caller's logits, and its argmax the host's tokens
-    const bool split_lm = e->plan.lm.S > 1;
-    ST_TRY(upload_inputs(e, tokens, valid, seq_lens, e->hist_cap, split_lm ? nullptr : logits));
+    // caller's logits where it can, and its argmax the host's tokens
+    const bool split_lm = e->plan.lm.S > 1, copy_logits = logits && (split_lm || !device_buffer(e, logits));
+    ST_TRY(upload_inputs(e, tokens, valid, seq_lens, e->hist_cap, copy_logits ? nullptr : logits));
     ST_TRY(run_step(e));
     const int B = e->B;
     if (split_lm) HIP_TRY(hipMemcpyAsync(e->h_next, e->d_next, sizeof(int32_t) * B, hipMemcpyDeviceToHost, e->st));
-    if (split_lm && logits)
+    if (copy_logits)
         HIP_TRY(hipMemcpyAsync(logits, e->logits, sizeof(float) * (size_t)B * e->c.vocab, hipMemcpyDeviceToDevice,
                                e->st));
     HIP_TRY(hipStreamSynchronize(e->st));
@@ -1648,8 +1659,11 @@ extern "C" corun_status corun_prefill_chunk(corun_engine *e, const int32_t *toke
     }
     HIP_TRY(launch_rmsnorm(e->pf_x + last, e->pf_part + last, dense_S, (long long)Lp * H, 1, H, e->final_norm,
                            c.rms_eps, e->pf_hlast, st, lf));
-    HIP_TRY(proj(e, e->pf_hlast, H, W_LM_HEAD, 0, pl, 1, last_logits ? last_logits : e->pf_logits, 0, c.vocab,
-                 HeadOut{e->pf_amax}));
+    const bool copy_logits = last_logits && !device_buffer(e, last_logits);
+    HIP_TRY(proj(e, e->pf_hlast, H, W_LM_HEAD, 0, pl, 1, last_logits && !copy_logits ? last_logits : e->pf_logits, 0,
+                 c.vocab, HeadOut{e->pf_amax}));
+    if (copy_logits)
+        HIP_TRY(hipMemcpyAsync(last_logits, e->pf_logits, sizeof(float) * c.vocab, hipMemcpyDeviceToDevice, st));
     HIP_TRY(launch_argmax_partials(e->pf_amax, 1, gemm_col_blocks(c.vocab), nullptr, e->pf_next, e->h_next, st));
     HIP_TRY(hipStreamSynchronize(st));
     if (token_out) *token_out = e->h_next[0];
@@ -1763,8 +1777,12 @@ extern "C" corun_status corun_prefill_batch(corun_engine *e, const int32_t *toke
     HIP_TRY(launch_rmsnorm(e->pf_x, e->pf_part, dense_S, (long long)Lp * H, Lp, H, e->final_norm, c.rms_eps, e->pf_h,
                            st, fold_of(e, pmb, c.n_layers)));
     HIP_TRY(launch_gather_last_rows(e->pf_h, e->pf_seq, n, H, e->pf_hlast, st));
-    HIP_TRY(proj(e, e->pf_hlast, H, W_LM_HEAD, 0, pl, n, last_logits ? last_logits : e->pf_logits, 0, c.vocab,
-                 HeadOut{e->pf_amax}));
+    const bool copy_logits = last_logits && !device_buffer(e, last_logits);
+    HIP_TRY(proj(e, e->pf_hlast, H, W_LM_HEAD, 0, pl, n, last_logits && !copy_logits ? last_logits : e->pf_logits, 0,
+                 c.vocab, HeadOut{e->pf_amax}));
+    if (copy_logits)
+        HIP_TRY(hipMemcpyAsync(last_logits, e->pf_logits, sizeof(float) * (size_t)n * c.vocab,
+                               hipMemcpyDeviceToDevice, st));
     HIP_TRY(launch_argmax_partials(e->pf_amax, n, gemm_col_blocks(c.vocab), nullptr, e->pf_next, e->h_next, st));
     HIP_TRY(hipStreamSynchronize(st));
     std::memcpy(tokens_out, e->h_next, sizeof(int32_t) * n);
