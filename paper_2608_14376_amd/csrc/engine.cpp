@@ -286,15 +286,6 @@ Plan make_plan(const corun_model_cfg *c, const corun_kv *kv, int B, const corun_
         p.down = Proj{H, c->expert_ffn, 1, c->expert_ffn, 0};
         p.moe_slots = c->n_experts + (B * c->top_k + 15) / 16;
     }
-    // gate/up at 128 < B <= 256 whose 256 x 128 tiles fit one round: those, no
-    // split-K, SwiGLU in the epilogue, instead of 256 x 256 tiles with split-K
-    // and a SwiGLU kernel (24576 x 4096 at B = 256: 67 against 71 + 11 us)
-    if (so == 0 && bo == 0 && !bi && c->n_experts == 0 && B > 128 && B <= 256 && p.gu.bm == 256 && p.gu.bn == 256 &&
-        p.gu.S > 1 && (p.gu.N + 127) / 128 <= 256) {
-        p.gu.bn = 128;
-        p.gu.S = 1;
-        p.gu.Kc = p.gu.K;
-    }
     // lm_head: never split (its epilogue selects the argmax partials) except
     // under the split override test aid; the 64-row tile has no argmax epilogue
     p.lm = choose_proj(c->vocab, H, B, so > 0 ? so : 1, 0, bo == 64 ? 0 : bo, bi);
