@@ -355,7 +355,7 @@ def main():
         else:
             s.add_argument("--pmc", required=True)
             s.add_argument("--trace", required=True)
-            s.add_argument("--kernel", default="k_gemm_dma", help="kernel name(s), comma-separated")
+            s.add_argument("--kernel", default="k_gemm_dma,k_gemm_wide", help="kernel name(s), comma-separated")
             s.add_argument("--label", action="append", default=[],
                            help="grid=name (mfma) or grid=name=weight_bytes (fetch)")
     a = ap.parse_args()
