@@ -1018,7 +1018,11 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_dma(const uint16_t *__restrict
 //    burst and the matrix cores do not wait for instruction issue;
 //  * loads through a buffer resource with the K offset in a scalar register:
 //    no per-load 64-bit address arithmetic in vector registers;
-//  * one barrier per 64 K elements, before the stage's last K step.
+//  * one barrier per 64 K elements, before the stage's last K step, and ahead
+//    of it a wait for the next stage alone, also in the last NST stages: with
+//    the whole ring awaited there, splits of few stages lost up to 1 us a
+//    launch (128 x 128 at M = 128, 8 splits of 4096 x 4096: 13.0 -> 12.6 us;
+//    151936 x 4096 at M = 256 on 256 x 128: 401 -> 397).
 // Measured (bf16 normal data, same box, old -> new tile): 256 x 256 at
 // M = 8192 over 24576 x 4096 1490 -> 1300 us, 4096 x 12288 691 -> 602,
 // 6144 x 4096 356 -> 312; 256 x 128 1685 -> 1435; 128 x 128 1932 -> 1654.
@@ -1229,7 +1233,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_wide(const uint16_t *__restric
 #pragma unroll
             for (int q = 0; q < (i == NST - 1 ? HALF : OPS); ++q) dma(q, i, i * BK);
     if (nk >= NST) __builtin_amdgcn_s_waitcnt(vmcnt_imm((NST - 2) * OPS + HALF));
-    else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    else wait_stages<OPS, NST - 2>(max(nk - 1, 0));
     lds_barrier();
     Frags f0, f1;
     {
@@ -1259,7 +1263,8 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_wide(const uint16_t *__restric
         pslot = slot;
         slot = nslot;
     }
-    // the last NST stages: nothing further to begin
+    // the last NST stages: nothing further to begin; stage i + 1 is awaited
+    // with the nk - 2 - i stages behind it still in flight
     if (i + NST - 1 < nk)
 #pragma unroll
         for (int q = HALF; q < OPS; ++q) dma(q, pslot, (i + NST - 1) * BK);
@@ -1267,7 +1272,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_wide(const uint16_t *__restric
         step(f0, f1, true, slot, 1, 0, 0, 0, 0);
         step(f1, f0, true, slot, 2, 0, 0, 0, 0);
         step(f0, f1, true, slot, 3, 0, 0, 0, 0);
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+        wait_stages<OPS, NST - 2>(max(nk - 2 - i, 0));
         __builtin_amdgcn_s_waitcnt(0xC07F);
         lds_barrier();
         __builtin_amdgcn_sched_barrier(0);

@@ -74,3 +74,28 @@ def test_default_plan_against_the_oracle(n):
     ref, _ = oracle.prefill(host_model(Wc), oracle_kv(K, V), 0, prompt)
     assert row_rel_err(last.cpu().numpy(), ref) <= TOL
     eng.close()
+
+
+@pytest.mark.parametrize("ffn", [64, 128, 192, 256, 320])
+def test_chains_shorter_than_the_ring(ffn):
+    """The down projection over one to five 64-element stages, on rings of
+    four (128 x 128), three (256 x 128) and two (256 x 256) stages: chains that
+    end before the ring is full, with its last slot and one or two later.  The
+    k, v of layer 1 carry layer 0's down products; the 64-row tile, another
+    kernel, gives the bits."""
+    cfg = wl.config("small128", hidden=2048, ffn=ffn)
+    opt = corun.options(max_prefill_len=4100, bi_prefill=True)
+    tiles = {64: (64, 128), 129: (128, 128), 2050: (256, 128), 4100: (256, 256)}
+    for n, t in tiles.items():
+        p = corun.describe_prefill_plan(cfg, n, opt)["down"]
+        assert (p["m_tile"], p["n_tile"], p["split_k"]) == (*t, 1), (n, p)
+    W = to_device(wl.make_weights(cfg, seed=87))
+    K, V = wl.make_kv_contiguous(cfg, 2, 4112, seed=88, device=DEV)
+    eng = corun.Engine(cfg, W, 2, K, V, opt=opt)
+    prompt = wl.make_prompt(cfg["vocab"], 4100, seed=89)
+    eng.prefill(prompt, 0)
+    for n in (64, 129, 2050):
+        eng.prefill(prompt[:n], 1)
+        for c in (K[1], V[1]):
+            assert torch.equal(c[1, :, :n].view(torch.int16), c[0, :, :n].view(torch.int16)), n
+    eng.close()
