@@ -3767,8 +3767,10 @@ __device__ __forceinline__ SamplePart sample_part(const float *__restrict__ l, i
     }
     const double M = div_by(lmax, T, rT);             // the largest l / T: the quotient keeps the order
     double S = 0.0;
-    if (lmax != -INFINITY)                            // all -inf: no weight, whatever the other parts hold
+    if (lmax != -INFINITY)
         for (int v = v0 + tid; v < v1; v += 256) S += exp(div_by(l[v], T, rT) - M);
+    else                                              // only -inf and NaN: no weight whatever the other parts hold, or NaN
+        for (int v = v0 + tid; v < v1; v += 256) S += __builtin_isnan(l[v]) ? (double)l[v] : 0.0;
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) S += __shfl_xor(S, off, 64);
     __syncthreads();                                  // every thread has read red

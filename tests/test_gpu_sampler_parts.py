@@ -48,3 +48,38 @@ def test_parts_match_the_oracle(vocab):
     tok2, lp2 = corun.sample_noalloc(x, valid, pos, seeds, T)
     assert np.array_equal(tok, tok2) and np.array_equal(lp.view(np.int32), lp2.view(np.int32))
     eng.close()
+
+
+def test_nan_reaches_the_log_probability():
+    """A NaN column never wins, but the row's log-probability is NaN wherever
+    it stands: in a part of nothing else, of -inf besides, or of finite
+    columns; -inf alone is only weightless.  Sampled and greedy rows."""
+    vocab, part = 49168, 16384
+    cfg = wl.config("tiny", n_layers=1, vocab=vocab)
+    nan, ninf = np.float32(np.nan), np.float32(-np.inf)
+    rng = np.random.default_rng(97)
+    l = np.tile(rng.normal(0, 2.5, vocab).astype(np.float32), (10, 1))
+    for r in (0, 5):
+        l[r, part: 2 * part] = nan                    # a part of NaN
+        l[r + 1, part: 2 * part] = ninf               # of -inf and one NaN
+        l[r + 1, part + 777] = nan
+        l[r + 2, 2 * part + 5] = nan                  # of finite columns and one NaN
+        l[r + 3, 3 * part:] = nan                     # the short last part
+        l[r + 4, part: 2 * part] = ninf               # no NaN
+    rows = len(l)
+    T = np.array([0.7] * 5 + [0.0] * 5, np.float32)
+    valid, pos = np.ones(rows, np.uint8), np.arange(rows, dtype=np.int32)
+    seeds = rng.integers(0, 1 << 63, rows, dtype=np.uint64)
+    K, V = wl.make_kv_contiguous(cfg, rows, 16, seed=98, device=DEV)
+    eng = corun.Engine(cfg, to_device(wl.make_weights(cfg, seed=99)), rows, K, V)
+    x = torch.from_numpy(l).to(DEV)
+    for tok, lp in (eng.sample(x, valid, pos, seeds, T), corun.sample_noalloc(x, valid, pos, seeds, T)):
+        for r in range(rows):
+            # without the NaN columns: the same winner
+            ot, olp = oracle.sample(np.where(np.isnan(l[r]), ninf, l[r]), int(seeds[r]), int(pos[r]), float(T[r]))
+            assert tok[r] == ot, (r, tok[r], ot)
+            if np.isnan(l[r]).any():
+                assert np.isnan(lp[r]), (r, lp[r])
+            else:
+                assert abs(float(lp[r]) - olp) <= 1e-6 * max(1.0, abs(olp)), (r, lp[r], olp)
+    eng.close()
