@@ -3640,9 +3640,12 @@ hipError_t launch_prefill_attn(const uint16_t *q, int n, int p0, int nq, int nkv
 //  * a column's score needs two fp64 logarithms only if it can win.  With
 //    s = 1 - u, -ln u >= s, so g <= -ln s and the score is below b (the
 //    wavefront's best so far) for certain once s > exp(l / T - b).  The test
-//    is made in fp32 with s rounded down to 26 bits and a margin of 1e-3,
-//    far above its own error; a NaN or a tie never rejects.  A few columns of
-//    each wavefront's thousands pass.
+//    is made in fp32 with s rounded down to 26 bits and a margin of 1e-3;
+//    its own error is below 1e-5 as long as |b| < 1e10 (the product with the
+//    rounded reciprocal is off by at most 2^-52 |l / T|), and past that (tiny
+//    T, infinities) no column is rejected.  A NaN never rejects.  A column
+//    whose score rounds to b itself is the later one, which loses the tie.  A
+//    few columns of each wavefront's thousands pass.
 //  * l / T is a product with the fp64 reciprocal and one correction step
 //    (q' = q + (l - q T) / T, correctly rounded: Markstein, IBM J. Res. Dev.
 //    34, 1990) instead of a division per column and pass.
@@ -3725,6 +3728,7 @@ __device__ __forceinline__ SamplePart sample_part(const float *__restrict__ l, i
         bz = (double)bl;
     } else {
         double b = -INFINITY;                         // the wavefront's best score
+        float margin = INFINITY;                      // infinite: no column is rejected
         for (int v = v0 + tid; v < v1; v += 256) {
             const float lf = l[v];
             lmax = fmaxf(lmax, lf);
@@ -3732,7 +3736,7 @@ __device__ __forceinline__ SamplePart sample_part(const float *__restrict__ l, i
             philox4x32_10(c, k0, k1);
             const float s = (float)(0x3FFFFFFu - (c[0] >> 6)) * 0x1p-26f;   // <= 1 - u but for its own rounding
             const float d = (float)__builtin_fma((double)lf, rT, -b);
-            if (!(s > __builtin_amdgcn_exp2f(d * 1.44269504f) * 1.001f)) {
+            if (!(s > __builtin_amdgcn_exp2f(d * 1.44269504f) * margin)) {
                 better_d(bz, bi, div_by(lf, T, rT) + gumbel_noise(c[0], c[1]), v);
             }
             // the wavefront's new best, where some lane has one (lanes' trip
@@ -3744,6 +3748,7 @@ __device__ __forceinline__ SamplePart sample_part(const float *__restrict__ l, i
 #pragma unroll
                 for (int off = 1; off < 64; off <<= 1) m = fmax(m, __shfl_xor(m, off, 64));
                 b = m;
+                margin = fabs(b) < 1e10 ? 1.001f : INFINITY;
             }
         }
     }

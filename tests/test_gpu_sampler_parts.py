@@ -83,3 +83,23 @@ def test_nan_reaches_the_log_probability():
             else:
                 assert abs(float(lp[r]) - olp) <= 1e-6 * max(1.0, abs(olp)), (r, lp[r], olp)
     eng.close()
+
+
+@pytest.mark.parametrize("T", [1e-12, 1e-13, 1e-14, 1e-15])
+def test_tiny_temperatures_on_flat_rows(T):
+    """Equal logits over a temperature so small that the noise is a few units
+    of l / T's last place: every column's score counts, and ties go to the
+    earlier column."""
+    vocab, rows = 400, 512
+    cfg = wl.config("tiny", n_layers=1, vocab=vocab)
+    rng = np.random.default_rng(101)
+    l = np.repeat(rng.uniform(1, 20, rows).astype(np.float32)[:, None], vocab, 1)
+    valid, pos = np.ones(rows, np.uint8), rng.integers(0, 1 << 20, rows).astype(np.int32)
+    seeds = rng.integers(0, 1 << 63, rows, dtype=np.uint64)
+    K, V = wl.make_kv_contiguous(cfg, rows, 16, seed=102, device=DEV)
+    eng = corun.Engine(cfg, to_device(wl.make_weights(cfg, seed=103)), rows, K, V)
+    tok, lp = eng.sample(torch.from_numpy(l).to(DEV), valid, pos, seeds, np.full(rows, T, np.float32))
+    want = [oracle.sample(l[r], int(seeds[r]), int(pos[r]), float(np.float32(T))) for r in range(rows)]
+    assert [int(t) for t in tok] == [t for t, _ in want]
+    assert np.allclose(lp, [p for _, p in want], rtol=1e-6, atol=0)
+    eng.close()
