@@ -69,10 +69,10 @@ hipError_t launch_moe_gemm(const uint16_t *A, int lda, int row_div, const uint16
 // The same product on the pipelined kernels (K % 64 == 0), weights row-major
 // per expert or tile-packed per expert (packed; w_expert_stride in elements of
 // the packed copy), one tile per (128 columns, tile slot): 32 x 128 for
-// tile_rows = 16; 64, 128 or 256 (packed only) the wide tile of that many
-// rows.  Every output is one K chain whatever the tile: the same bits.
-// With act (packed gate/up-interleaved copies, N % 128 == 0) the epilogue
-// writes act[a][j] = SwiGLU of feature j (bf16, ld ldo) instead of out.
+// tile_rows = 16; 64 or 128 (packed only) the wide tile of that many rows.
+// Every output is one K chain whatever the tile: the same bits.  With act
+// (packed gate/up-interleaved copies, N % 128 == 0) the epilogue writes
+// act[a][j] = SwiGLU of feature j (bf16, ld ldo) instead of out.
 hipError_t launch_moe_gemm_dma(const uint16_t *A, int lda, int row_div, const uint16_t *W, long long w_expert_stride,
                                bool packed, int N, int K, const int32_t *list, const int32_t *tiles, int n_slots,
                                int tile_rows, float *out, uint16_t *act, int ldo, hipStream_t st);

@@ -3183,9 +3183,6 @@ hipError_t launch_moe_gemm_dma(const uint16_t *A, int lda, int row_div, const ui
             case 128:
                 return wide_launch<128, 128, 2, 2, 4, EPI, true, true>(grid, st, A, lda, W, 128, N, K, K, out, 0, ldo,
                                                                       HeadOut{}, act, et);
-            case 256:
-                return wide_launch<256, 128, 3, 2, 4, EPI, true, true>(grid, st, A, lda, W, 256, N, K, K, out, 0, ldo,
-                                                                      HeadOut{}, act, et);
             default:
                 return hipErrorInvalidValue;
             }
@@ -3812,7 +3809,7 @@ __device__ __forceinline__ void sample_merge(const SamplePart *parts, int np, co
     }
 }
 
-__global__ __launch_bounds__(256) void k_sample_part(const float *__restrict__ logits, long long ld, int V, int rows,
+__global__ __launch_bounds__(256) void k_sample_part(const float *__restrict__ logits, long long ld, int V,
                                                      const uint8_t *__restrict__ valid, const int32_t *__restrict__ pos,
                                                      const uint64_t *__restrict__ seed, const float *__restrict__ temp,
                                                      SamplePart *__restrict__ parts)
@@ -3883,7 +3880,7 @@ hipError_t launch_sample(const float *logits, long long ld, int rows, int V, con
         KLAUNCH(k_sample_row, dim3(rows), dim3(1024), 0, st, logits, ld, V, valid, pos, seed, temp, token, logprob);
         return hipGetLastError();
     }
-    KLAUNCH(k_sample_part, dim3(np, rows), dim3(256), 0, st, logits, ld, V, rows, valid, pos, seed, temp, scratch);
+    KLAUNCH(k_sample_part, dim3(np, rows), dim3(256), 0, st, logits, ld, V, valid, pos, seed, temp, scratch);
     KLAUNCH(k_sample_merge, dim3(rows), dim3(64), 0, st, logits, ld, V, np, valid, temp, scratch, token, logprob);
     return hipGetLastError();
 }
