@@ -742,12 +742,20 @@ corun_status moe_expert_down(corun_engine *e, const MoeBufs &m, int l)
 // model, us per prefill with 16 / 64 / 128 / 256 rows: 100 tokens 619 / 619 /
 // 651 / 741, 200 741 / 698 / 710 / 840, 500 990 / 849 / 840 / 990, 1200 1573 /
 // 1159 / 1103 / 1255, 3000 3065 / 1950 / 1808 / 1967, 8000 7909 / 4765 / 4401 /
-// 4626.
+// 4626.  Where the two expert launches of 16-row tiles have few workgroups the
+// chip has room for them, and a tile's latency is what counts (a ring of four
+// stages against two): over seven models of 4 to 128 experts, 512 to 2048
+// wide, they win up to about 1700 workgroups (16 experts, hidden 512, 130
+// tokens, 288 workgroups: 189 against 205 / 207; 16 experts, hidden 2048, 130
+// tokens, 1344: 272 against 281 / 283, and 200 tokens, 1848: 319 against 292 /
+// 293).
 int moe_tile_rows(const corun_engine *e, int rows)
 {
     const corun_model_cfg &c = e->c;
     if (e->packed[W_EXP_GATE_UP].empty() || e->packed[W_EXP_DOWN].empty()) return 16;
     if ((long long)rows * c.top_k * std::max(c.hidden, c.expert_ffn) * 2 >= (1ll << 32)) return 16;   // 32-bit row offsets
+    const long long slots = c.n_experts + (long long)rows * c.top_k / 16;
+    if (slots * ((2 * c.expert_ffn + 127) / 128 + (c.hidden + 127) / 128) <= 1700) return 16;
     const double per = (double)rows * c.top_k / c.n_experts;
     return per <= 8 ? 16 : per <= 24 ? 64 : 128;
 }

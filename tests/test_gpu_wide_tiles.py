@@ -21,13 +21,17 @@ from tests.gpu_helpers import DEV, check_routing, host_model, oracle_kv, row_rel
 pytestmark = pytest.mark.gpu
 TOL = 2e-2
 LENS = {"small128": (1, 64, 65, 127, 128, 129, 255, 256, 257, 319, 320, 321, 640, 641),
-        "small_moe": (31, 32, 33, 95, 96, 97, 512, 513)}
+        "small_moe": (31, 32, 33, 95, 96, 97, 512, 513),
+        # 64 experts of 4 assignments a row over 18 column tiles: 16-row expert
+        # tiles to 128 rows (8 per expert), 64-row ones to 384, 128-row ones above
+        "moe64": (33, 127, 128, 129, 200, 383, 384, 385, 513)}
+CONFIGS = {"moe64": dict(n_experts=64, hidden=2048)}
 LONGEST = 700
 
 
 @pytest.mark.parametrize("name", sorted(LENS))
 def test_prefix_bits_at_the_tile_edges(name):
-    cfg = wl.config(name)
+    cfg = wl.config("small_moe", **CONFIGS[name]) if name in CONFIGS else wl.config(name)
     Wc = wl.make_weights(cfg, seed=81)
     Wg = to_device(Wc)
     K, V = wl.make_kv_contiguous(cfg, 2, 704, seed=82)
