@@ -3625,11 +3625,16 @@ hipError_t launch_prefill_attn(const uint16_t *q, int n, int p0, int nq, int nkv
 // and log-probability (of the chosen token under softmax(l / T), softmax(l)
 // when greedy) in fp64.
 //
-// The row is cut into parts of sample_part_size(V) columns (a function of V
-// alone), a workgroup of 256 threads per part: its best score, its largest
-// logit M_p and S_p = sum exp(l / T - M_p) in a fixed tree (sequential per
-// thread, 64-lane butterfly, the four wavefronts in order).  The merge takes
-// the best score, M = max M_p and sum_p S_p exp(M_p - M) in part order.
+// The row is cut into 4 ceil(V / 65536) nearly equal parts of sample_part_size(V)
+// columns (a function of V alone), a workgroup of 256 threads per part: its
+// best score, its largest logit M_p and S_p = sum exp(l / T - M_p) in a fixed
+// tree (sequential per thread, 64-lane butterfly, the four wavefronts in
+// order).  The merge takes the best score, M = max M_p and sum_p S_p
+// exp(M_p - M) in part order.  Four parts at least, and a multiple of four:
+// the form without scratch runs them four at a time, and a row of up to 65536
+// columns is spread over four CUs.  Parts of 16384 columns whatever V left a
+// row of 16400 to one of them: greedy, 256 rows 87 us a call, without scratch
+// 94, now 56 and 72 (a workgroup of 1024 threads per row took 68 and 73).
 //
 // What bounds it is arithmetic, so the parts do less of it than one workgroup
 // per row evaluating everything did (162 live rows of 151936 on 162 of the
@@ -3695,9 +3700,10 @@ __device__ __forceinline__ double div_by(float lf, double T, double rT)
 
 __host__ __device__ constexpr int sample_part_size(int V)
 {
-    return 16384 * ((V + 16384 * SAMPLE_MAX_PARTS - 1) / (16384 * SAMPLE_MAX_PARTS));
+    const int q = 4 * ((V - 1) / 65536 + 1) < SAMPLE_MAX_PARTS ? 4 * ((V - 1) / 65536 + 1) : SAMPLE_MAX_PARTS;
+    return ((V - 1) / q / 256 + 1) * 256;
 }
-__host__ __device__ constexpr int sample_parts(int V) { return (V + sample_part_size(V) - 1) / sample_part_size(V); }
+__host__ __device__ constexpr int sample_parts(int V) { return (V - 1) / sample_part_size(V) + 1; }
 
 // Columns [v0, v1) of one row, by 256 threads (tid 0 .. 255, four whole
 // wavefronts); red: their 4 x 3 doubles of LDS.  Every group of a workgroup

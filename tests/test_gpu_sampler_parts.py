@@ -1,7 +1,8 @@
-"""The sampler's row parts (16384 columns each) and the test that spares most
-columns their fp64 logarithms: vocabularies at the parts' edges, masked
-(-inf) columns and parts, ties, flat rows, huge and tiny temperatures and
-logits, against the oracle; the scratch-free form gives the same bits."""
+"""The sampler's row parts (4 ceil(V / 65536) of a multiple of 256 columns) and
+the test that spares most columns their fp64 logarithms: vocabularies at the
+parts' edges, masked (-inf) columns and parts, ties, flat rows, huge and tiny
+temperatures and logits, against the oracle; the scratch-free form gives the
+same bits."""
 import numpy as np
 import pytest
 import torch
@@ -14,7 +15,7 @@ from tests.gpu_helpers import DEV, to_device
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("vocab", [16, 16368, 16384, 16400, 32768, 49168])
+@pytest.mark.parametrize("vocab", [16, 256, 272, 1024, 1040, 16368, 16384, 16400, 32768, 49168, 65536, 65552])
 def test_parts_match_the_oracle(vocab):
     cfg = wl.config("tiny", n_layers=1, vocab=vocab)
     Wg = to_device(wl.make_weights(cfg, seed=95))
@@ -54,7 +55,7 @@ def test_nan_reaches_the_log_probability():
     """A NaN column never wins, but the row's log-probability is NaN wherever
     it stands: in a part of nothing else, of -inf besides, or of finite
     columns; -inf alone is only weightless.  Sampled and greedy rows."""
-    vocab, part = 49168, 16384
+    vocab, part = 65520, 16384
     cfg = wl.config("tiny", n_layers=1, vocab=vocab)
     nan, ninf = np.float32(np.nan), np.float32(-np.inf)
     rng = np.random.default_rng(97)
