@@ -256,3 +256,16 @@ def test_prefill_plan_is_a_function_of_the_length_only():
     assert {300, 600} & split, split
     moe = corun.describe_prefill_plan(wl.config("moe"), 300)
     assert moe["router"]["N"] == 128 and moe["gate_up"]["N"] == 0
+
+
+@pytest.mark.parametrize("name", ["8b", "32b", "moe", "small128"])
+def test_prefill_splits_within_blocks_of_64_rows(name):
+    """Within the 64 rows after a multiple of 64 no tile count changes and the
+    estimates are linear in the length, so the splits only fall: the engine
+    sizes its partial sums from the blocks' ends where those agree."""
+    c = wl.config(name)
+    projs = ("qkv", "o", "gate_up", "down", "router")
+    for first in range(129, 4200, 64):
+        splits = [[corun.describe_prefill_plan(c, n)[p]["split_k"] for p in projs] for n in range(first, first + 64)]
+        for a, b in zip(splits, splits[1:]):
+            assert all(x >= y for x, y in zip(a, b)), (first, a, b)
