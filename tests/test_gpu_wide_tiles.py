@@ -5,9 +5,11 @@ With batch-invariant prefill every projection output is one MFMA chain over K
 in order, whatever tile it is computed in, and causal attention gives a
 position the same bits whatever follows it.  So the k, v of a prompt's first n
 positions are bit-identical whether the prompt is prefilled at n tokens or
-longer -- at every row count around the tiles' edges (64, 128, 256, 320), the
-expert tile's (16, 64, 128 rows) and the two-launch dispatch's (more than 2048
-assignments).  Against the oracle: relative 2e-2 on the last logits.
+longer.  The small models run the 64- and 128-row tiles and the expert tiles
+(16, 64, 128 rows; two-launch dispatch above 2048 assignments) at row counts
+around their edges; a model 4096 wide runs every tile, with one row or all but
+one of its last row tile and half or a quarter of its last column tile.
+Against the oracle: relative 2e-2 on the last logits.
 """
 import numpy as np
 import pytest
@@ -42,6 +44,8 @@ def test_prefix_bits_at_the_tile_edges(name):
     last = torch.empty(cfg["vocab"], dtype=torch.float32, device=DEV)
     eng.prefill(prompt, 0, last)
     for n in LENS[name]:
+        for c in Kd + Vd:
+            c[1].zero_()
         eng.prefill(prompt[:n], 1)
         for l in range(cfg["n_layers"]):
             for c in (Kd[l], Vd[l]):
@@ -99,7 +103,62 @@ def test_chains_shorter_than_the_ring(ffn):
     prompt = wl.make_prompt(cfg["vocab"], 4100, seed=89)
     eng.prefill(prompt, 0)
     for n in (64, 129, 2050):
+        for c in K + V:
+            c[1].zero_()
         eng.prefill(prompt[:n], 1)
         for c in (K[1], V[1]):
             assert torch.equal(c[1, :, :n].view(torch.int16), c[0, :, :n].view(torch.int16)), n
+    eng.close()
+
+
+# rows: tile of qkv for heads of 128 and of 64, of o and down, of gate/up
+WIDE = {64: ((64, 128), (64, 128), (64, 128), (64, 128)),
+        65: ((128, 128), (128, 128), (128, 128), (128, 128)),
+        257: ((128, 128), (128, 128), (128, 128), (256, 256)),
+        641: ((256, 128), (128, 128), (128, 128), (256, 128)),
+        897: ((256, 128), (256, 128), (128, 128), (256, 128)),
+        1537: ((256, 256), (256, 256), (256, 128), (320, 256)),
+        2049: ((256, 256), (256, 256), (256, 256), (320, 256)),
+        2881: ((320, 256), (256, 256), (256, 256), (320, 256)),
+        3199: ((320, 256), (320, 256), (256, 256), (320, 256)),
+        4161: ((256, 128), (256, 128), (320, 256), (256, 256)),
+        4479: ((256, 256), (256, 128), (320, 256), (320, 256))}
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("head_dim", [128, 64])
+def test_every_wide_tile(head_dim, paged):
+    """The QKV epilogue (heads of 128) or fp32 sums (64) over column counts of
+    22.5 and 20.25 tiles of 256, SwiGLU over 86.5, fp32 sums of o and down: k, v
+    of both layers against the longest prompt's, in another slot and, paged,
+    on another cache layout."""
+    heads = 15 if head_dim == 128 else 27
+    cfg = wl.config("small128", hidden=4096, n_heads=heads, n_kv_heads=heads, head_dim=head_dim, ffn=11072)
+    longest, cap, page = max(WIDE), 4480, 16
+    opt = corun.options(max_prefill_len=longest, bi_prefill=True)
+    for n, (qkv128, qkv64, odown, gu) in WIDE.items():
+        p = corun.describe_prefill_plan(cfg, n, opt)
+        want = {"qkv": qkv128 if head_dim == 128 else qkv64, "o": odown, "down": odown, "gate_up": gu}
+        assert {k: (p[k]["m_tile"], p[k]["n_tile"]) for k in want} == want, n
+    W = wl.make_weights(cfg, seed=104, device=DEV)
+    prompt = wl.make_prompt(cfg["vocab"], longest, seed=105)
+    K, V = wl.make_kv_contiguous(cfg, 2, cap, seed=106, device=DEV)
+    eng = corun.Engine(cfg, W, 2, K, V, opt=opt)
+    eng.prefill(prompt, 0)
+    if paged:
+        eng.close()
+        pages = np.random.default_rng(107).permutation(2 * cap // page).astype(np.int32).reshape(2, -1)
+        Kp, Vp = wl.make_kv_paged(cfg, pages.size, page, 108, device=DEV)
+        eng = corun.Engine(cfg, W, 2, Kp, Vp, opt=opt, layout=corun.KV_PAGED, page_size=page,
+                           page_table=torch.from_numpy(pages).to(DEV))
+        eng.set_page_table_host(pages)
+        row = torch.from_numpy(pages[1]).to(DEV).long()
+    for n in WIDE:
+        for c in Kp + Vp if paged else [x[1] for x in K + V]:
+            c.zero_()
+        eng.prefill(prompt[:n], 1)
+        for i, ref in enumerate(K + V):
+            got = (Kp + Vp)[i][row].transpose(0, 1).reshape(heads, -1, head_dim) if paged else ref[1]
+            assert torch.equal(got[:, :n].contiguous().view(torch.int16),
+                               ref[0, :, :n].contiguous().view(torch.int16)), (n, i)
     eng.close()
