@@ -89,9 +89,10 @@ int mt_for(int M) { return M <= 16 ? 1 : (M <= 32 ? 2 : 4); }
 //    decode projections (128 < M <= 256, N >= 16384: gate/up, lm_head);
 //    split-K up to one round of at most 256 workgroups, each split keeping
 //    at least 512 K elements.
-//  * M > 256 (prefill), K % 64 == 0: the pipelined kernel with the tile
-//    (256 x 256, 256 x 128, 128 x 128) and split-K of least estimated time
-//    (waves of 256 workgroups, per-tile wave costs, the partials' traffic).
+//  * M > 256, K % 64 == 0 (decode; a prefill of more than 128 rows takes
+//    choose_wide): the pipelined kernel with the tile (256 x 256, 256 x 128,
+//    128 x 128) and split-K of least estimated time (waves of 256 workgroups,
+//    per-tile wave costs, the partials' traffic).
 //  * otherwise (or bm_override > 0): the LDS-tiled kernel with a 128-row
 //    tile (or bm_override), split-K to about two workgroups per CU.
 // Batch-invariant mode (bi): no split-K and, when K % 64 == 0, the
@@ -122,15 +123,17 @@ Proj choose_proj(int N, int K, int M, int split_override, int max_split, int bm_
         S = std::min(S, std::max(1, K / 512));
         align = 64;
     } else if (M > 256 && bm_override <= 0 && K % 64 == 0) {
-        // Prefill-sized M: the tile and split-K with the least estimated
-        // time, calibrated on this GPU's pipelined kernel.  A launch runs in
-        // waves of 256 workgroups; a wave costs c x K / S with c = 1.69,
+        // The tile and split-K with the least estimated time.  A launch runs
+        // in waves of 256 workgroups; a wave costs c x K / S with c = 1.69,
         // 1.0, 0.62 for 256 x 256, 256 x 128, 128 x 128 tiles (a 256 x 128
-        // wave over 4096 K elements took 68.5 us), and each split beyond the
+        // wave over 4096 K elements: 68.5 us), and each split beyond the
         // first adds a set of fp32 partials that is written and folded again
-        // (8 bytes per output at about 5 TB/s).  Against measured times at
-        // M = 512 .. 8192 the estimate picks the fastest tile, or one within
-        // a few percent.
+        // (8 bytes per output at about 5 TB/s).  The costs are those of the
+        // tiles before k_gemm_wide; with its tiles the choice costs 4% more
+        // than the fastest of them on average over o and down of the 8B, 32B
+        // and MoE shapes at 300 to 1024 rows (31% at worst: o of 8B at 300
+        // rows, 39 us with 256 x 128 in four splits against 29 with 128 x
+        // 128 in two, the following norm included).
         struct Cand {
             int bm, bn;
             double c;
@@ -205,11 +208,15 @@ Proj choose_proj(int N, int K, int M, int split_override, int max_split, int bm_
 // the cost grows with the square of the filled part), `fixed` of them whatever
 // K (ring fill, epilogue); every split beyond the first adds a set of fp32
 // partials written and folded again (8 bytes per output at about 5 TB/s).
-// Over 4 projections of the 8B shape at 15 lengths from 300 to 8192 rows
-// (128 x 128 at 300 x 4096 x 4096: 25 us; 320 x 256 at 4200 x 4096 x 12288:
-// 341 us against 519 with 256 x 256, which needs a second round for 16 of its
-// 272 tiles) the choice costs 2% more than the fastest measured one on
-// average.
+// The constants were fitted to four projections of the 8B shape, before the 256
+// x 128 tile had eight wavefronts and the qkv tiles their epilogue.  With the
+// tiles as they are, over the projections of the 8B, 32B and MoE shapes at 16
+// lengths from 150 to 16384 rows, each with the kernel that folds its splits,
+// the choice costs 2.2% more than the fastest measured one on average (320 x
+// 256 for down of 8B at 4200 rows: 383 us against 567 with 256 x 256, which
+// needs a second round for 16 of its 272 tiles) and 28% at worst (the same at
+// 512 and 1024 rows: 128 x 128 in two splits and in one, 80 and 137 us,
+// against 63 and 107 with 256 x 128 in four and in two).
 Proj choose_wide(int N, int K, int M, int max_split)
 {
     Proj p;

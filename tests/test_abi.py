@@ -214,12 +214,10 @@ def test_options_take_only_flags():
     corun.describe_plan(c, kv, 4, corun.options(no_weight_pack=True, qkv_epilogue=2))
 
 
-def test_prefill_tiles_follow_the_wave_estimate():
-    """M > 256 takes the tile and split-K of least estimated time (waves of
-    256 workgroups, per-tile wave costs, split partials' traffic): the
-    choices the standalone measurements favour at these 8B shapes.  The
-    decode plan at B = 512 and 1024 runs the same rule as a prefill of that
-    many rows (describe_plan stops at B = 1024)."""
+def test_decode_tiles_above_256_rows_follow_the_wave_estimate():
+    """Decode batches of more than 256 rows take the tile and split-K of
+    choose_proj's estimate (waves of 256 workgroups, per-tile wave costs,
+    split partials' traffic)."""
     c = wl.config("8b")
 
     def plan(M):
@@ -234,6 +232,26 @@ def test_prefill_tiles_follow_the_wave_estimate():
     for p in (p512, p1024):                          # every split keeps at least 512 K elements
         for name, K in (("qkv", 4096), ("o", 4096), ("gate_up", 4096), ("down", 12288)):
             assert K // p[name][2] >= 512, (name, p[name])
+
+
+def test_prefill_tiles_of_the_8b_shape():
+    """Prefill of more than 128 rows takes choose_wide's tile and split-K: one
+    round where its workgroups fit one, the tile that wastes least of the last
+    round where they do not; gate/up never splits (its epilogue applies
+    SwiGLU).  (qkv, o, gate/up, down) as (rows, columns, splits):"""
+    want = {200: ((128, 128, 2), (128, 128, 4), (256, 128, 1), (128, 128, 4)),
+            600: ((128, 128, 1), (128, 128, 1), (320, 256, 1), (256, 128, 2)),
+            1024: ((256, 128, 1), (128, 128, 1), (256, 128, 1), (128, 128, 1)),
+            2048: ((256, 256, 1), (256, 128, 1), (256, 256, 1), (256, 128, 1)),
+            4200: ((256, 256, 1), (320, 256, 1), (256, 256, 1), (320, 256, 1)),
+            32768: ((320, 256, 1), (256, 256, 1), (320, 256, 1), (256, 256, 1))}
+    for n, tiles in want.items():
+        p = corun.describe_prefill_plan(wl.config("8b"), n)
+        got = tuple((p[k]["m_tile"], p[k]["n_tile"], p[k]["split_k"]) for k in ("qkv", "o", "gate_up", "down"))
+        assert got == tiles, (n, got)
+    for name in ("8b", "32b", "small128"):
+        for n in range(65, 3000, 37):
+            assert corun.describe_prefill_plan(wl.config(name), n)["gate_up"]["split_k"] == 1, (name, n)
 
 
 def test_prefill_plan_is_a_function_of_the_length_only():
