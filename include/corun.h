@@ -58,10 +58,9 @@ enum { CORUN_KV_CONTIGUOUS = 0, CORUN_KV_PAGED = 1 };
 /* Model shape.  n_experts = top_k = expert_ffn = 0 selects a dense SwiGLU
  * MLP of width `ffn`; otherwise every layer routes each token to top_k of
  * n_experts SwiGLU experts of width expert_ffn (softmax over all experts,
- * top_k, renormalised).  Requirements: hidden, ffn, expert_ffn multiples of
- * 16 (a K dimension may have a tail of 8, e.g. ffn = 688); head_dim 64 or
- * 128; n_heads a multiple of n_kv_heads with n_heads / n_kv_heads <= 16;
- * vocab a multiple of 16. */
+ * top_k, renormalised).  Requirements: hidden a multiple of 256; ffn and
+ * expert_ffn multiples of 16; head_dim 64 or 128; n_heads / n_kv_heads 1, 2,
+ * 4, 8 or (head_dim 128) 16; vocab a multiple of 16. */
 typedef struct {
     int32_t n_layers, hidden, n_heads, n_kv_heads, head_dim, ffn, vocab;
     int32_t n_experts, top_k, expert_ffn;
@@ -401,7 +400,7 @@ enum {
     CORUN_K_QKV_POST = 8,     /* QKV epilogue: RoPE + KV append (no kernel where the attention kernel
                                  applies it: corun_options.qkv_epilogue) */
     CORUN_K_SWIGLU = 9,       /* SwiGLU epilogue (no kernel where the gate/up projection's epilogue applies it:
-                                 packed weights without split-K) */
+                                 projections without split-K from packed weights or, above 64 rows, from any) */
     CORUN_K_ARGMAX = 10,      /* greedy argmax */
     CORUN_K_MOE_ROUTER = 11,  /* MoE: router projection, top-k routing and dispatch (3 kernels) */
     CORUN_K_COUNT = 12

@@ -1005,8 +1005,9 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_dma(const uint16_t *__restrict
 // Like k_gemm_dma, both operands stream global -> LDS through a ring of NST
 // stages and every output element is one chain of v_mfma_f32_32x32x16_bf16
 // over K in order, so the tile changes no bit of a result.  What differs is
-// what bounded k_gemm_dma's large tiles (62% of the matrix cores' cycles busy
-// at M = 8192, the rest in instruction issue):
+// what bounded k_gemm_dma's large tiles, instruction issue (at M = 8192 about
+// two other vector instructions beside each product; now 0.5 without a fused
+// epilogue, 1.3 with one):
 //  * stages of 64 K elements, so a load instruction covers whole 128-byte
 //    lines (8 rows x 128 bytes, not 16 x 64);
 //  * fragments double-buffered per K step (FM + FN registers' worth, not a
@@ -1026,8 +1027,8 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_dma(const uint16_t *__restrict
 // Measured (bf16 normal data, same box, old -> new tile): 256 x 256 at
 // M = 8192 over 24576 x 4096 1490 -> 1300 us, 4096 x 12288 691 -> 602,
 // 6144 x 4096 356 -> 312; 256 x 128 1685 -> 1435; 128 x 128 1932 -> 1654.
-// At these rates the card is at its power limit (1.6 GHz under this load; the
-// matrix instruction alone, no memory, reaches 1.77 PFLOP/s on such data).
+// At these rates the clock falls to 1.8 GHz (2.3 where the matrix cores idle),
+// and the cores are busy 71% of its cycles.
 //
 // Wavefront tiles are 64 columns wide (FN = 2), as the argmax and SwiGLU
 // epilogues need.
@@ -1406,8 +1407,9 @@ hipError_t wide_launch(dim3 grid, hipStream_t st, const uint16_t *A, int lda, co
 // The wide tile bm x bn; false if there is none.  128 x 128 tiles that fill
 // at most one round of the 256 CUs, or that stream their weights for a single
 // row of tiles, take a ring of four stages (loads in flight; M = 128 over
-// 151936 x 4096: 323 against 355 us), others two stages, so that two
-// workgroups share a CU (24576 x 4096 at M = 8192: 1654 against 1868 us).
+// 151936 x 4096: 321 us, 355 with two stages; k_gemm_dma's tile took 323),
+// others two stages, so that two workgroups share a CU (24576 x 4096 at M =
+// 8192: 1654 against 1868 us).
 template <int EPI, class... Args>
 bool wide_tile(int bm, int bn, hipError_t &e, bool one_row, dim3 grid, Args... args)
 {
@@ -3638,7 +3640,7 @@ hipError_t launch_prefill_attn(const uint16_t *q, int n, int p0, int nq, int nkv
 //
 // What bounds it is arithmetic, so the parts do less of it than one workgroup
 // per row evaluating everything did (162 live rows of 151936 on 162 of the
-// 256 CUs: 388 us; parts and merge: 124 us):
+// 256 CUs: 388 us; parts and merge: 113 us):
 //  * a column's score needs two fp64 logarithms only if it can win.  With
 //    s = 1 - u, -ln u >= s, so g <= -ln s and the score is below b (the
 //    wavefront's best so far) for certain once s > exp(l / T - b).  The test

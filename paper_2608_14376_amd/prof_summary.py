@@ -29,6 +29,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CLOCK_GHZ = 2.4
 SIMDS = 1024
+XCDS = 8
 
 
 def source_sha() -> str:
@@ -71,7 +72,10 @@ def pmc_dispatches(path, counters):
         did = int(r["Dispatch_Id"])
         name = short(r["Kernel_Name"])
         g = grid(r)
-        by.setdefault(did, (name, g, {}))[2][r["Counter_Name"]] = float(r["Counter_Value"])
+        c = by.setdefault(did, (name, g, {}))[2]
+        c[r["Counter_Name"]] = float(r["Counter_Value"])
+        if "Start_Timestamp" in r:
+            c["us"] = (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3
     return [by[k] for k in sorted(by)]
 
 
@@ -292,10 +296,12 @@ def cmd_prefill(a):
     lines = header(a)
     lines += [f"# busy = SQ_VALU_MFMA_BUSY_CYCLES / (duration x {CLOCK_GHZ} GHz x {SIMDS} SIMDs) (32 cycles per "
               "32x32x16 bf16 MFMA);",
+              f"# GHz = GRBM_GUI_ACTIVE / {XCDS} XCDs / duration in the counter run (kernels one at a time), of cyc = the busy",
+              f"# cycles against GRBM_GUI_ACTIVE / {XCDS} x {SIMDS} SIMDs;",
               "# VALU / MFMA and LDS / MFMA are instruction-count ratios (SQ_INSTS_VALU counts the MFMAs too);",
               "# durations from the kernel-trace run, counters from the counter run, matched dispatch by dispatch",
-              "", f"{'op':12s} {'kernel':16s} {'dispatches':>10s} {'us':>9s} {'busy':>6s} {'TFLOP/s':>8s} "
-                  f"{'VALU/MFMA':>9s} {'LDS/MFMA':>8s} {'conflicts/LDS':>13s}"]
+              "", f"{'op':12s} {'kernel':16s} {'dispatches':>10s} {'us':>9s} {'busy':>6s} {'TFLOP/s':>8s} {'GHz':>5s} "
+                  f"{'of cyc':>6s} {'VALU/MFMA':>9s} {'LDS/MFMA':>8s} {'conflicts/LDS':>13s}"]
     total_us = sum(sum(v) for v in dur.values())
     for nm in ops + ["attention", "lm_head"]:
         if nm not in dur:
@@ -306,7 +312,11 @@ def cmd_prefill(a):
         busy = mean("SQ_VALU_MFMA_BUSY_CYCLES") / (us * 1e-6 * CLOCK_GHZ * 1e9 * SIMDS)
         tf = flops.get(nm, 0.0) / us / 1e6
         lds = mean("SQ_INSTS_LDS")
-        lines.append(f"{nm:12s} {kern[nm]:16s} {len(dur[nm]):10d} {us:9.2f} {100 * busy:5.1f}% {tf:8.1f} "
+        gui, run_us = mean("GRBM_GUI_ACTIVE") / XCDS, mean("us")
+        ghz = gui / run_us / 1e3 if run_us else 0.0
+        cyc = mean("SQ_VALU_MFMA_BUSY_CYCLES") / (gui * SIMDS) if gui else 0.0
+        lines.append(f"{nm:12s} {kern[nm]:16s} {len(dur[nm]):10d} {us:9.2f} {100 * busy:5.1f}% {tf:8.1f} {ghz:5.2f} "
+                     f"{100 * cyc:5.1f}% "
                      f"{mean('SQ_INSTS_VALU') / mf if mf else 0:9.2f} {lds / mf if mf else 0:8.2f} "
                      f"{mean('SQ_LDS_BANK_CONFLICT') / lds if lds else 0:13.3f}")
     rest = sorted(((nm, sum(v)) for nm, v in dur.items() if nm not in ops + ["attention", "lm_head"]),
