@@ -130,8 +130,8 @@ WIDE = {64: ((64, 128), (64, 128), (64, 128), (64, 128)),
 def test_every_wide_tile(head_dim, paged):
     """The QKV epilogue (heads of 128) or fp32 sums (64) over column counts of
     22.5 and 20.25 tiles of 256, SwiGLU over 86.5, fp32 sums of o and down: k, v
-    of both layers against the longest prompt's, in another slot and, paged,
-    on another cache layout."""
+    of both layers against the longest prompt's, in another slot, paged on
+    another cache layout, contiguous also as a batch of prompts."""
     heads = 15 if head_dim == 128 else 27
     cfg = wl.config("small128", hidden=4096, n_heads=heads, n_kv_heads=heads, head_dim=head_dim, ffn=11072)
     longest, cap, page = max(WIDE), 4480, 16
@@ -142,10 +142,16 @@ def test_every_wide_tile(head_dim, paged):
         assert {k: (p[k]["m_tile"], p[k]["n_tile"]) for k in want} == want, n
     W = wl.make_weights(cfg, seed=104, device=DEV)
     prompt = wl.make_prompt(cfg["vocab"], longest, seed=105)
-    K, V = wl.make_kv_contiguous(cfg, 2, cap, seed=106, device=DEV)
-    eng = corun.Engine(cfg, W, 2, K, V, opt=opt)
+    K, V = wl.make_kv_contiguous(cfg, 4, cap, seed=106, device=DEV)
+    eng = corun.Engine(cfg, W, 4, K, V, opt=opt)
     eng.prefill(prompt, 0)
-    if paged:
+    if not paged:   # 2881 rows of three prompts, each in its own slot
+        lens = (1500, 881, 500)
+        eng.prefill_batch([prompt[:n] for n in lens], np.array([2, 1, 3], np.int32))
+        for n, slot in zip(lens, (2, 1, 3)):
+            for c in K + V:
+                assert torch.equal(c[slot, :, :n].view(torch.int16), c[0, :, :n].view(torch.int16)), (n, slot)
+    else:
         eng.close()
         pages = np.random.default_rng(107).permutation(2 * cap // page).astype(np.int32).reshape(2, -1)
         Kp, Vp = wl.make_kv_paged(cfg, pages.size, page, 108, device=DEV)
